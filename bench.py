@@ -84,7 +84,8 @@ def kernel_work(wl, B: int) -> dict:
     exp_f = 2.0 * EXP_SLOTS
     pair_fwd = (2.0 + exp_f + 1.0) if wl.dtype == "bf16" else (2.0 + exp_f + 3.0)
     pair_bwd = (2.0 + exp_f + 1.0) if wl.dtype == "bf16" else (2 * (2.0 + exp_f) + 11.0)
-    # saved per row by the matrix-core forward: (o, Z) and the backward's row sums (W1, W2)
+    # saved per row by the matrix-core forward, counted as four floats: (o, Z) and two row sums (the
+    # kernels keep the sums' one combination that the query gradient needs, so three are moved)
     stats = 4 * r * 4 if wl.dtype == "bf16" else 0
     # h, and its second plane when the activations are held as f16 or as bf16 hi + lo
     h_out = r * eb * (2 if wl.act_mode in ("f16", "hilo") else 1)
@@ -293,8 +294,9 @@ def mfma_counter_rates(wl, tag: str, prof: dict) -> dict:
 
 
 def attention_exp_rate(wl, tag: str, B: int, prof: dict):
-    """Exponentials per second of the attention kernels (one per (query, key) pair in the
-    forward and one in the backward) against the chip's exponential rate and against the
+    """(query, key) pairs per second of the attention kernels as exponentials per second (one
+    per pair in the forward and one in the backward; the panel sums evaluate far fewer, so the
+    rate can pass the chip's) against the chip's exponential rate and against the
     measured exp + add rate."""
     if not wl.attention:
         return None

@@ -95,7 +95,7 @@ size_t eb(const rdcn_handle* h) { return h->bf16 ? 2 : 4; }
 
 // Per layer: [v|q|k] (float with the attention term, else storage; plus a second
 // plane of v without it), h and its second plane (attention only), the attention row
-// statistics [o | Z | W1 | W2] (float, bf16 storage with attention), t, x_{l+1} and its
+// statistics [o | Z | D] (float, bf16 storage with attention), t, x_{l+1} and its
 // second plane (l < L-1). Second planes exist with activation modes 1 (the lo part of a
 // bf16 hi + lo pair) and 2: x_{l+1} is then f16 in X and its bf16 copy (the weight
 // gradient's operand) in X2, h is bf16 in H and f16 in H2, and v (no attention) bf16 in
@@ -119,7 +119,7 @@ SavedLayout saved_layout(const rdcn_handle* h, int64_t B) {
         s.P2[l] = off; off += (sp && !h->attn) ? al(B * r * e) : 0;
         s.H[l] = off; off += h->attn ? al(B * (size_t)h->hr * e) : 0;
         s.H2[l] = off; off += (sp && h->attn) ? al(B * r * e) : 0;
-        s.A[l] = off; off += (h->attn && h->bf16) ? al(B * 4 * r * 4) : 0;
+        s.A[l] = off; off += (h->attn && h->bf16) ? al(B * 3 * r * 4) : 0;
         s.T[l] = off; off += al(B * d * e);
         s.X[l] = off; off += more ? al(B * d * e) : 0;  // x_{l+1}
         s.X2[l] = off; off += (sp && more) ? al(B * d * e) : 0;

@@ -36,9 +36,8 @@ hipError_t launch_quantize_rows(int64_t rows, int D, const void* tables, int8_t*
 
 namespace rdcn {
 
-// bf16 storage: the forward writes o_i, Z_i and the row sums W1_i = sum_j e_ij v_j k_j,
-// W2_i = sum_j e_ij k_j of every row to stats ([o | Z | W1 | W2] per sample, row
-// stride 4 r) and the backward reads them back.
+// bf16 storage: the forward writes o_i, Z_i and D_i = sum_j A_ij (v_j - o_i) k_j of every row
+// to stats ([o | Z | D] per sample, row stride 3 r) and the backward reads them back.
 // H2: optional second plane of h: its f16 value (h2_f16) or the lo part of a bf16
 // hi + lo pair; f16 values beyond range set bit 2 of *err.
 hipError_t launch_attn_fwd(int64_t B, int r, float alpha, float beta, float tau, const void* P, int64_t ldp, void* H,

@@ -1,0 +1,95 @@
+"""The bf16 attention kernels' two forms (panel sums and direct sums, chosen per sample by
+its range of scores) against the fp64 oracle, where the choice and its tiles have edges.
+
+One layer without depth: q, k and v come from x0 and W through exact bf16 products with
+float sums, so the float weight gradients see the attention through two bf16 roundings
+only (gt or x0's products, and [gv|gq|gk] or h: 2^-9 each) and must be within 2^-8 of the
+oracle in norm; softmax errors of one f16 rounding (2^-11) stay below that. The key
+gradient sum_i A_ij a_i (v_j - o_i) nearly cancels where the softmax is close to one-hot
+(o_i = v_j): the rounding of its terms is bounded by 2^-11 of their magnitudes' sum, which
+is added to its bar.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_helpers import need_gpu, relerr, to_np
+from paper_2402_06859_amd.step import DeviceBatch
+from paper_2402_06859_amd.synth import Workload, make_inputs
+
+pytestmark = pytest.mark.gpu
+TOL = 2.0 ** -8
+
+
+def compare(wl, edit=None):
+    inp = make_inputs(wl, bias_std=0.1)
+    if edit is not None:
+        edit(inp)
+    db = DeviceBatch(wl, inp)
+    db.gather()
+    db.forward()
+    db.backward()
+    torch.cuda.synchronize()
+    x0 = to_np(db.x0)
+    W, U, b = ([w.float().numpy() for w in inp[k]] for k in ("w_down", "u", "bias"))
+    args = (wl.alpha, wl.beta, wl.temperature)
+    xL = oracle.forward(x0, W, U, b, *args)
+    gx0, gW, gU, gb = oracle.backward(x0, W, U, b, inp["grad_out"].float().numpy(), *args)
+    r = wl.rank
+    # magnitudes of the key gradient's terms against the gradient, from q, k, v and gh in float64
+    P = x0.astype(np.float64) @ W[0].T.astype(np.float64)
+    v, q, k = (P[:, i * r:(i + 1) * r] for i in range(3))
+    gh = (inp["grad_out"].float().numpy().astype(np.float64) * x0) @ U[0]
+    S = q[:, :, None] * k[:, None, :] / wl.temperature
+    A = np.exp(S - S.max(2, keepdims=True))
+    A /= A.sum(2, keepdims=True)
+    o = np.einsum("bij,bj->bi", A, v)
+    w = A * (gh * q / wl.temperature)[:, :, None]
+    gk = (w * (v[:, None, :] - o[:, :, None])).sum(1)
+    mag = (np.abs(w) * (np.abs(v[:, None, :]) + np.abs(o[:, :, None]))).sum(1)
+    tol = {"gk": TOL + 2.0 ** -11 * np.linalg.norm(mag) / max(np.linalg.norm(gk), 1e-3 * np.linalg.norm(gh))}
+    errs = {"x": relerr(to_np(db.x_out), xL), "gx0": relerr(to_np(db.grad_x0), gx0),
+            "gU": relerr(to_np(db.g_u[0]), gU[0])}
+    scale = 1e-3 * np.linalg.norm(gW[0])  # (a part that vanishes exactly is measured on the whole)
+    for i, n in enumerate(("gv", "gq", "gk")):
+        ref = gW[0][i * r:(i + 1) * r]
+        errs[n] = np.linalg.norm(to_np(db.g_w_down[0])[i * r:(i + 1) * r] - ref) / max(np.linalg.norm(ref), scale)
+    print(wl.rank, wl.batch, wl.temperature, {n: "%.2g" % e for n, e in errs.items()}, "gk bar %.2g" % tol["gk"],
+          flush=True)
+    assert all(e <= tol.get(n, TOL) for n, e in errs.items()), errs
+
+
+# rank: 24, 40 and 120 (always direct), 128 and 136 (one tile and the next), 256 | 264 (one
+# wave | four), 512 | 520 (one tile per wave | two), 1024; batches leave waves of the last
+# workgroup without a sample. Temperatures: one group of panels, several, several sweeps
+# over the entries, and so sharp that samples take the direct sums (rank 256 at 0.08 mixes both).
+@pytest.mark.parametrize("rank,batch,tau", [
+    (24, 9, 1.0), (40, 7, 0.5), (120, 7, 1.0), (128, 6, 1.0), (136, 5, 0.3), (256, 6, 4.0), (256, 33, 0.08),
+    (256, 5, 0.02), (264, 3, 1.0), (264, 3, 0.1), (512, 3, 0.2), (520, 3, 1.0), (1024, 3, 1.0), (1024, 24, 0.05),
+    (1024, 2, 0.02)])
+def test_forms(rank, batch, tau):
+    need_gpu()
+    compare(Workload("att", 21, batch, 4, 20_000, 150, 16, 64, 1, rank, True, "bf16", "sum", 1.1, temperature=tau))
+
+
+@pytest.mark.parametrize("rank", [40, 256, 600])
+@pytest.mark.parametrize("what", ["keys", "queries", "values", "one_sided"])
+def test_degenerate_ranges(rank, what):
+    """All keys equal (a range of width 0), all queries zero, all values zero, and queries and
+    keys of one sign far from zero (a shifted range)."""
+    need_gpu()
+
+    def edit(inp):
+        w = inp["w_down"][0]
+        if what == "keys":
+            w[2 * rank:] = w[2 * rank]
+        elif what == "queries":
+            w[rank:2 * rank] = 0
+        elif what == "values":
+            w[:rank] = 0
+        else:  # a strong common direction on the dense inputs
+            inp["dense"][:] = 1
+            w[rank:, 64:] += 0.08
+
+    compare(Workload("att_deg", 22, 5, 4, 20_000, 150, 16, 64, 1, rank, True, "bf16", "sum", 1.1), edit)
