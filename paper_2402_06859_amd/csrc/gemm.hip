@@ -1,4 +1,4 @@
-// bf16 MFMA GEMMs with fused epilogues for gfx950, plus a float VALU GEMM for
+// bf16 MFMA GEMMs with fused epilogues for gfx950, plus a float MFMA GEMM for
 // float-storage models.
 //
 // C[m, n] = scale * sum_k A(m, k) B(n, k), float accumulate. Each operand is
@@ -794,53 +794,113 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 2 : 1, WM * WN == 8 ? 2 : 8)))
     block_epilogue<BM, BN, WM, WN, M32, T, MLP, P::THREADS, ST * P::STAGE_ELEMS>(g, c.m0, c.n0, z, acc, smem, tid);
 }
 
-// Float VALU GEMM (float-storage models): 64 x 64 tile, 4 x 4 outputs per
-// thread (4 consecutive columns), operands addressed through (row, k) strides.
-__global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
-    constexpr int T64 = 64, TK = 16;
-    __shared__ float sA[TK][T64 + 1];
-    __shared__ float sB[TK][T64 + 1];
-    const int tid = threadIdx.x;
-    const int tiles_n = (int)((g.N + T64 - 1) / T64);
-    const int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * T64, n0 = (int64_t)(blockIdx.x % tiles_n) * T64;
+// Float GEMM (float-storage models) on the float matrix instruction v_mfma_f32_16x16x4_f32
+// (float products and sums). Operands go from global memory straight to registers: lane
+// (q, i) holds the four k values 4 q .. 4 q + 3 of row i of a 16-row fragment (one 16-byte
+// load where k is contiguous, four 4-byte loads of 64 contiguous bytes per 16 lanes where
+// rows are), which are the operands of four matrix instructions; the order of k within a
+// step of 16 is the same permutation on both sides. A workgroup owns a 32 SM x 32 SN block:
+// SM x SN waves side by side, and KW such groups that split the k steps among them (group w
+// takes steps w, w + KW, ...), whose sums are added in group order through LDS.
+//
+// These products are small (the smallest workload's are 512 x 32 x 160 and 32 x 160 x 512),
+// so what bounds them is the latency of a wave's chain of loads: the k split shortens it,
+// and all loads of FK steps are in flight together. Before (64 x 64 blocks, one wave column
+// of vector FMAs, operands through LDS 16 k at a time): 92 us for 32 x 160 x 512 (3 blocks),
+// 25 us for 512 x 32 x 160; now 7.2 and 6.9 us (a bare launch takes about 2).
+constexpr int FK = 4;  // k steps (of 16) whose loads are in flight together
+
+template <bool KS>
+__device__ __forceinline__ f32x4_t frag_f32(const float* __restrict__ x, int64_t ld, int64_t row, int64_t k, int64_t kend) {
+    f32x4_t v;
+    if (!KS) {  // kend and k are multiples of 4: a piece is inside or past the end
+        v = *(const f32x4_t*)(x + row * ld + (k < kend ? k : 0));
+        if (k >= kend) v = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = x[(k + e < kend ? k + e : 0) * ld + row];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = k + e < kend ? v[e] : 0.f;
+    }
+    return v;
+}
+
+template <int SM, int SN, int KW, bool AKS, bool BKS>
+__global__ __launch_bounds__(64 * SM * SN * KW) void k_gemm_f32(GemmArgs g) {
+    constexpr int THREADS = 64 * SM * SN * KW, BM = 32 * SM, BN = 32 * SN, CP = BN + 4;
+    __shared__ __attribute__((aligned(16))) float cs[KW][BM * CP];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int kw = wave / (SM * SN), sw = wave % (SM * SN), wm = sw / SN, wn = sw % SN;
+    const int tiles_n = (int)((g.N + BN - 1) / BN);
+    const int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * BM, n0 = (int64_t)(blockIdx.x % tiles_n) * BN;
     const int z = blockIdx.z;
-    const int64_t kchunk = ((g.K + (int64_t)gridDim.z * TK - 1) / ((int64_t)gridDim.z * TK)) * TK;
-    const int64_t kbeg = z * kchunk;
-    const int64_t kend = kbeg + kchunk < g.K ? kbeg + kchunk : g.K;
-    const float* A = (const float*)g.a;
-    const float* B = (const float*)g.b;
-    const int64_t a_sr = g.a_kstrided ? 1 : g.lda, a_sk = g.a_kstrided ? g.lda : 1;
-    const int64_t b_sr = g.b_kstrided ? 1 : g.ldb, b_sk = g.b_kstrided ? g.ldb : 1;
-    const int tr = tid / 16, tc = tid % 16;  // rows tr*4.., cols tc*4..
-    float acc[4][4] = {};
-    for (int64_t k0 = kbeg; k0 < kend; k0 += TK) {
-        for (int e = tid; e < TK * T64; e += 256) {
-            const int kk = e / T64, rr = e % T64;
-            const int64_t gk = k0 + kk;
-            sA[kk][rr] = (m0 + rr < g.M && gk < kend) ? A[(m0 + rr) * a_sr + gk * a_sk] : 0.f;
-            sB[kk][rr] = (n0 + rr < g.N && gk < kend) ? B[(n0 + rr) * b_sr + gk * b_sk] : 0.f;
-        }
-        __syncthreads();
+    const int64_t kchunk = ((g.K + (int64_t)gridDim.z * 16 - 1) / ((int64_t)gridDim.z * 16)) * 16;
+    const int64_t kbeg = z * kchunk, kend = kbeg + kchunk < g.K ? kbeg + kchunk : g.K;
+    const int i = lane & 15, q4 = 4 * (lane >> 4);
+    int64_t am[2], bn[2];  // rows past the end re-read the last one; their results are not stored
 #pragma unroll
-        for (int kk = 0; kk < TK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = sA[kk][tr * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = sB[kk][tc * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
+    for (int t = 0; t < 2; ++t) {
+        const int64_t m = m0 + 32 * wm + 16 * t + i, n = n0 + 32 * wn + 16 * t + i;
+        am[t] = m < g.M ? m : g.M - 1;
+        bn[t] = n < g.N ? n : g.N - 1;
     }
+    f32x4_t acc[2][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t m = m0 + tr * 4 + i;
-        const int64_t n = n0 + tc * 4;
-        if (m < g.M && n < g.N) epilogue4<float>(g, m, n, z, acc[i]);
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int64_t k0 = kbeg + 16 * kw; k0 < kend; k0 += 16 * KW * FK) {
+        f32x4_t af[FK][2], bf[FK][2];
+#pragma unroll
+        for (int u = 0; u < FK; ++u) {
+            const int64_t k = k0 + 16 * KW * u + q4;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                af[u][t] = frag_f32<AKS>((const float*)g.a, g.lda, am[t], k, kend);
+                bf[u][t] = frag_f32<BKS>((const float*)g.b, g.ldb, bn[t], k, kend);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < FK; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[u][b][e], af[u][a][e], acc[a][b], 0, 0, 0);
     }
+    // lane holds C[m = 16 a + i][n = 16 b + q4 .. + 3]
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            *(f32x4_t*)(&cs[kw][(32 * wm + 16 * a + i) * CP + 32 * wn + 16 * b + q4]) = acc[a][b];
+    __syncthreads();
+    for (int c = threadIdx.x; c < BM * BN / 4; c += THREADS) {
+        const int row = c / (BN / 4), col = c % (BN / 4) * 4;
+        const int64_t m = m0 + row, n = n0 + col;
+        if (m >= g.M || n >= g.N) continue;
+        f32x4_t s = *(const f32x4_t*)(&cs[0][row * CP + col]);
+#pragma unroll
+        for (int w = 1; w < KW; ++w) s += *(const f32x4_t*)(&cs[w][row * CP + col]);
+        float v[4] = {s.x, s.y, s.z, s.w};
+        epilogue4<float>(g, m, n, z, v);
+    }
+}
+
+template <int SM, int SN, int KW>
+hipError_t launch_f32(const GemmArgs& g, int splits, hipStream_t s) {
+    const int64_t tiles = ((g.M + 32 * SM - 1) / (32 * SM)) * ((g.N + 32 * SN - 1) / (32 * SN));
+    const dim3 grid((unsigned)tiles, 1, (unsigned)splits), block(64 * SM * SN * KW);
+    if (g.a_kstrided) {
+        if (g.b_kstrided) hipLaunchKernelGGL((k_gemm_f32<SM, SN, KW, true, true>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((k_gemm_f32<SM, SN, KW, true, false>), grid, block, 0, s, g);
+    } else {
+        if (g.b_kstrided) hipLaunchKernelGGL((k_gemm_f32<SM, SN, KW, false, true>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((k_gemm_f32<SM, SN, KW, false, false>), grid, block, 0, s, g);
+    }
+    return hipGetLastError();
 }
 
 // out[m, n] = scale_out * sum_z part[z, m, n], summed in z order.
@@ -892,14 +952,22 @@ hipError_t launch_tile(const GemmArgs& g, int splits, hipStream_t s) {
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split, int split_blocks) {
     GemmPlan p;
     if (!bf16) {
-        p.bm = p.bn = 64;
-    } else {
-        const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
-        // Weight gradients (split-K allowed) take big tiles, which halve the operand
-        // re-reads, and recover parallelism by splitting the batch dimension.
-        if (t128 >= 240 || (allow_split && M >= 128 && N >= 128)) p.bm = p.bn = 128;
-        else p.bm = p.bn = 64;
+        // 64 x 64 blocks (two groups of waves along k) once they fill half the chip, else
+        // 32 x 32 blocks whose eight waves split k; weight gradients of a long batch over few
+        // tiles split it over workgroups too, at least 1024 rows (128 per wave) each
+        const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t32 = ((M + 31) / 32) * ((N + 31) / 32);
+        p.bm = p.bn = t64 >= 128 ? 64 : 32;
+        const int64_t t = t64 >= 128 ? t64 : t32;
+        int64_t sp = allow_split && t < 256 ? 256 / t : 1;
+        if (sp > K / 1024) sp = K / 1024;
+        p.splits = (int)(sp < 1 ? 1 : sp > 16 ? 16 : sp);
+        return p;
     }
+    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    // Weight gradients (split-K allowed) take big tiles, which halve the operand
+    // re-reads, and recover parallelism by splitting the batch dimension.
+    if (t128 >= 240 || (allow_split && M >= 128 && N >= 128)) p.bm = p.bn = 128;
+    else p.bm = p.bn = 64;
     const int64_t tiles = ((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn);
     p.splits = 1;
     if (allow_split && tiles < 256) {
@@ -917,7 +985,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     // Large products (bound by the MFMA rate rather than by L2 -> LDS loads): eight
     // waves on 256-row blocks with 32 x 32 x 16 MFMAs, which halve the bytes loaded
     // per flop; 256 x 256 blocks when they still cover the chip, else 256 x 128.
-    if (bf16 && (double)M * (double)N * (double)K >= 8.0e9) {
+    if ((double)M * (double)N * (double)K >= 8.0e9) {
         // Per 64-deep K step a block needs max(MFMA time, load time): MFMA at ~3600
         // flop/clk per CU, loads at the ~24 B/clk per CU that L2 -> LDS sustains here.
         // A launch takes ceil(tiles / 256) rounds of that (one block per CU).
@@ -927,7 +995,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
             return std::ceil(tiles / 256.0) * (mfma > load ? mfma : load);
         };
         const double c256 = cost(256, 256), c128 = cost(256, 128);
-        const int64_t t128 = ((M + 255) / 256) * ((N + 127) / 128);
+        const int64_t t256 = ((M + 255) / 256) * ((N + 127) / 128);
         // Tiles in groups of four tile rows: the 32 blocks an XCD runs at once then
         // read 4 A panels and 8 B panels instead of 1-3 A panels and up to 32 B panels
         // (measured on the large workload's six products: 2-8% faster, none slower).
@@ -936,7 +1004,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
             p.splits = 1;
             p.stages = 2;
             p.group_m = 4;
-        } else if (t128 >= 128) {
+        } else if (t256 >= 128) {
             p.bm = 256;
             p.bn = 128;
             p.splits = 1;
@@ -951,9 +1019,7 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStrea
     if (g.M == 0 || g.N == 0) return hipSuccess;
     if (!bf16 && (g.epi == EPI_MLP_FWD || g.epi == EPI_MLP_BWD)) return hipErrorInvalidValue;
     if (!bf16) {
-        const int64_t tiles = ((g.M + 63) / 64) * ((g.N + 63) / 64);
-        hipLaunchKernelGGL(k_gemm_f32, dim3((unsigned)tiles, 1, (unsigned)p.splits), dim3(256), 0, s, g);
-        return hipGetLastError();
+        return p.bm == 64 ? launch_f32<2, 2, 2>(g, p.splits, s) : launch_f32<1, 1, 8>(g, p.splits, s);
     }
     GemmArgs ga = g;
     ga.group_m = p.group_m;

@@ -1,0 +1,42 @@
+"""Float models' products (all six of a layer) against the fp64 oracle at sizes around the
+blocks, the waves' split of k and the split of a long batch over workgroups.
+
+Bar: float products and sums over K <= 5000 terms; an error of sqrt(K) roundings of the
+terms' magnitude is below 1e-5 of the result's norm."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_helpers import need_gpu, relerr, to_np
+from paper_2402_06859_amd.step import DeviceBatch
+from paper_2402_06859_amd.synth import Workload, make_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+# batch (K of the weight gradients): 1, below and above one step of 16 and one pass of the
+# waves, several passes, long enough to be split over workgroups; rank and width: one
+# remainder, one block, 32-blocks and 64-blocks
+@pytest.mark.parametrize("batch,cat,dense,rank,attn", [
+    (1, 2, 4, 4, False), (17, 2, 8, 12, False), (130, 2, 8, 36, True), (515, 3, 20, 32, False), (2051, 4, 64, 64, False),
+    (4099, 2, 32, 20, False), (300, 60, 64, 128, True)])
+def test_products(batch, cat, dense, rank, attn):
+    need_gpu()
+    wl = Workload("f32", 31, batch, cat, 10_000, 100, 16, dense, 2, rank, attn, "f32", "mul", 1.1)
+    inp = make_inputs(wl, bias_std=0.1)
+    db = DeviceBatch(wl, inp)
+    db.gather()
+    db.forward()
+    db.backward()
+    torch.cuda.synchronize()
+    x0 = to_np(db.x0)
+    W, U, b = ([w.float().numpy() for w in inp[k]] for k in ("w_down", "u", "bias"))
+    args = (wl.alpha, wl.beta, wl.temperature)
+    xL = oracle.forward(x0, W, U, b, *args)
+    gx0, gW, gU, gb = oracle.backward(x0, W, U, b, inp["grad_out"].float().numpy(), *args)
+    errs = [relerr(to_np(db.x_out), xL), relerr(to_np(db.grad_x0), gx0)]
+    for l in range(wl.num_layers):
+        errs += [relerr(to_np(db.g_w_down[l]), gW[l]), relerr(to_np(db.g_u[l]), gU[l]), relerr(to_np(db.g_bias[l]), gb[l])]
+    print(batch, wl.d, rank, "max rel err %.2g" % max(errs), flush=True)
+    assert max(errs) <= 1e-5
