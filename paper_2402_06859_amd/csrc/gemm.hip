@@ -794,6 +794,142 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 2 : 1, WM * WN == 8 ? 2 : 8)))
     block_epilogue<BM, BN, WM, WN, M32, T, MLP, P::THREADS, ST * P::STAGE_ELEMS>(g, c.m0, c.n0, z, acc, smem, tid);
 }
 
+// ---------------------------------------------------------------------------
+// Few rows (a scoring request, a small training batch): C = A B^T with both operands
+// K-contiguous, too few 64 x 64 tiles to fill the chip and a long serial K loop in each.
+// A workgroup owns a small block of 16 TM x 16 TN outputs and its eight waves split the K
+// stages (wave w takes stages w, w + 8, ..): each wave streams its stages into a ring of
+// its own in LDS by direct global-to-LDS loads and waits on its own load count, so the K
+// loop has no barrier. (Loads straight to registers in the matrix operand's lane order
+// reach 15 B/clk per CU, four neighbouring lanes being four rows; the staging loads take
+// whole row pieces.) The waves' sums are added in wave order through LDS, 32 rows at a
+// time, where the fused epilogue runs.
+// ---------------------------------------------------------------------------
+constexpr int ST_KW = 8;
+
+template <int TM, int TN, int ST, int KB, typename T, bool MLP, bool F16>
+__global__ __launch_bounds__(64 * ST_KW) void k_gemm_stream(GemmArgs g) {
+    constexpr int BM = 16 * TM, BN = 16 * TN, CP = BN + 4, ROWS = BM < 32 ? BM : 32;
+    constexpr int STAGE = (BM + BN) * KB;                  // elements of one wave's stage
+    constexpr int NIA = BM * KB / 512, NIB = BN * KB / 512;  // load instructions per stage
+    static_assert(ST_KW * ROWS * CP * 4 <= ST_KW * ST * STAGE * 2, "the sums fit the rings");
+    __shared__ __attribute__((aligned(1024))) bf16_t smem[ST_KW * ST * STAGE];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tiles_n = (int)((g.N + BN - 1) / BN), tiles_m = (int)((g.M + BM - 1) / BM);
+    // consecutive blocks of an XCD walk the rows of one column of tiles: its B panel is
+    // read into that XCD's L2 once
+    const int t = xcd_remap(blockIdx.x, tiles_m * tiles_n);
+    const int64_t m0 = (int64_t)(t % tiles_m) * BM, n0 = (int64_t)(t / tiles_m) * BN;
+    f32x4_t acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    uint32_t aoff[NIA], boff[NIB];
+    const bool fast = (BM + 1.0) * (double)g.lda * 2.0 < 2.0e9 && (BN + 1.0) * (double)g.ldb * 2.0 < 2.0e9;
+    if (fast) {
+        stage_offsets<BM, false, 1, KB>(g.lda, g.M, m0, m0, 0, lane, aoff);
+        stage_offsets<BN, false, 1, KB>(g.ldb, g.N, n0, n0, 0, lane, boff);
+    }
+    const int nk = (int)((g.K + KB - 1) / KB), ntot = nk * (g.a2 ? 2 : 1);  // K stages of both planes of A
+    const int cnt = wave < ntot ? (ntot - wave + ST_KW - 1) / ST_KW : 0;     // this wave's
+    bf16_t* const ring = smem + wave * ST * STAGE;
+    auto issue = [&](int j, int slot) {
+        const int s = wave + ST_KW * j, plane = s >= nk;
+        const int64_t k0 = (int64_t)(s - plane * nk) * KB;
+        const bf16_t* a = (const bf16_t*)(plane ? g.a2 : g.a);
+        const bf16_t* b = (const bf16_t*)g.b;
+        bf16_t* const buf = ring + slot * STAGE;
+        if (fast && k0 + KB <= g.K) {
+            const void* sa = uniform_ptr(a + m0 * g.lda + k0);
+            const void* sb = uniform_ptr(b + n0 * g.ldb + k0);
+            const uint32_t la = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_addr(buf)), lb = la + BM * KB * 2;
+#pragma unroll
+            for (int u = 0; u < NIA; ++u) dma16_s(aoff[u], sa, la + 1024u * u);
+#pragma unroll
+            for (int u = 0; u < NIB; ++u) dma16_s(boff[u], sb, lb + 1024u * u);
+        } else {
+            stage_load<BM, false, 1, KB>(a, g.lda, g.M, m0, k0, g.K, buf, 0, lane);
+            stage_load<BN, false, 1, KB>(b, g.ldb, g.N, n0, k0, g.K, buf + BM * KB, 0, lane);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < ST - 1; ++u)
+        if (u < cnt) issue(u, u);
+    int slot = 0;
+    for (int j = 0; j < cnt; ++j) {
+        if (j + ST - 1 < cnt) {
+            issue(j + ST - 1, slot == 0 ? ST - 1 : slot - 1);  // (j + ST - 1) % ST
+            wait_vmcnt((NIA + NIB) * (ST - 1));
+        } else {
+            wait_vmcnt(0);
+        }
+        const bf16_t* const cur = ring + slot * STAGE;
+        slot = slot + 1 == ST ? 0 : slot + 1;
+#pragma unroll
+        for (int ks = 0; ks < KB; ks += 32) {
+            bf16x8_t af[TM], bf[TN];
+#pragma unroll
+            for (int a = 0; a < TM; ++a) af[a] = load_frag<BM, false, KB>(cur, 16 * a, ks, lane);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) bf[b] = load_frag<BN, false, KB>(cur + BM * KB, 16 * b, ks, lane);
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) acc[a][b] = mfma16x16x32<F16>(bf[b], af[a], acc[a][b]);
+        }
+        // the fragments are in registers before the next pass's loads overwrite their slot
+        wait_lgkm0();
+    }
+    const int i = lane & 15, q4 = 4 * (lane >> 4);
+    float* const cs = (float*)smem;
+    bool ovf = false;  // an output written as f16 overflowed
+#pragma unroll
+    for (int h = 0; h < BM / ROWS; ++h) {
+        __syncthreads();
+        // lane holds C[m = 16 a + i][n = 16 b + q4 .. + 3]
+#pragma unroll
+        for (int a = 0; a < ROWS / 16; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+                *(f32x4_t*)(cs + (wave * ROWS + 16 * a + i) * CP + 16 * b + q4) = acc[h * (ROWS / 16) + a][b];
+        __syncthreads();
+        for (int c = threadIdx.x; c < ROWS * (BN / 8); c += 64 * ST_KW) {
+            const int row = c / (BN / 8), col = c % (BN / 8) * 8;
+            const int64_t m = m0 + h * ROWS + row, n = n0 + col;
+            if (m >= g.M || n >= g.N) continue;
+            const float* const p = cs + row * CP + col;
+            f32x4_t s0 = *(const f32x4_t*)p, s1 = *(const f32x4_t*)(p + 4);
+#pragma unroll
+            for (int w = 1; w < ST_KW; ++w) {
+                s0 += *(const f32x4_t*)(p + w * ROWS * CP);
+                s1 += *(const f32x4_t*)(p + w * ROWS * CP + 4);
+            }
+            float v[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+            if constexpr (MLP) (void)mlp_epilogue8<T>(g, m, n, v, ovf);
+            else epilogue8<T>(g, m, n, 0, v, ovf);
+        }
+    }
+    if (ovf) atomicOr(g.err, ERR_BIT_F16_RANGE);
+}
+
+template <int TM, int TN, int ST, int KB>
+hipError_t launch_stream(const GemmArgs& g, hipStream_t s) {
+    if (g.a_kstrided || g.b_kstrided || g.epi == EPI_MLP_BWD || g.epi == EPI_PARTIAL) return hipErrorInvalidValue;
+    const int64_t tiles = ((g.M + 16 * TM - 1) / (16 * TM)) * ((g.N + 16 * TN - 1) / (16 * TN));
+    const dim3 grid((unsigned)tiles), block(64 * ST_KW);
+    const bool mlp = g.epi == EPI_MLP_FWD;
+    if (g.ops_f16) {
+        if (g.a2) return hipErrorInvalidValue;
+        if (mlp) hipLaunchKernelGGL((k_gemm_stream<TM, TN, ST, KB, bf16_t, true, true>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((k_gemm_stream<TM, TN, ST, KB, bf16_t, false, true>), grid, block, 0, s, g);
+    } else {
+        if (mlp) hipLaunchKernelGGL((k_gemm_stream<TM, TN, ST, KB, bf16_t, true, false>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((k_gemm_stream<TM, TN, ST, KB, bf16_t, false, false>), grid, block, 0, s, g);
+    }
+    return hipGetLastError();
+}
+
 // Float GEMM (float-storage models) on the float matrix instruction v_mfma_f32_16x16x4_f32
 // (float products and sums). Operands go from global memory straight to registers: lane
 // (q, i) holds the four k values 4 q .. 4 q + 3 of row i of a 16-row fragment (one 16-byte
@@ -1023,6 +1159,24 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStrea
     }
     GemmArgs ga = g;
     ga.group_m = p.group_m;
+    if (p.bm == 64 && p.splits == 1 && !g.a_kstrided && !g.b_kstrided) {
+        // The streamed blocks as long as one round of them (one or two per CU) covers the
+        // output: they finish a K loop in an eighth of the time, but each loads its own
+        // operands, so over more rounds the 64 x 64 blocks' reuse wins. us, streamed /
+        // 64 x 64, by tiles of the block (in the order below):
+        //   K 1856, N 768:   50 rows, 192 tiles 5.7 / 12.8;  256 rows, 192 tiles 6.9 / 13.1;
+        //                    512 rows, 192 tiles 9.5 / 13.0;  1024 rows, 384 tiles 18.1 / 13.4
+        //   K 4352, N 512:   64 rows, 128 tiles 5.7 / 22.7; 512 rows, 256 tiles 10.5 / 21.8;
+        //                    1024 rows, 256 tiles 18.5 / 22.1
+        //   K 10624, N 3072: 16 rows, 192 tiles 13.3 / 48.3; 50 rows, 192 tiles 17.5 / 48.5;
+        //                    128 rows, 192 tiles 33.5 / 48.6; 256 rows, 384 tiles 62.9 / 49.2
+        //   K 256, N 1856:   128 rows, 232 tiles 4.6 / 5.6; 256 rows, 464 tiles 6.9 / 5.8
+        // (64 x 32 blocks run shorter stages, which pay only on a deep K).
+        auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+        if (tiles(16, 16) <= 256) return launch_stream<1, 1, 2, 64>(ga, s);
+        if (tiles(32, 32) <= 256) return launch_stream<2, 2, 2, 64>(ga, s);
+        if (tiles(64, 32) <= 256 && g.K >= 1536) return launch_stream<4, 2, 2, 32>(ga, s);
+    }
     if (p.bm == 256) {
         if (p.bn == 256) return launch_tile<256, 256, 2, 2, 4, true, bf16_t>(ga, p.splits, s);
         return launch_tile<256, 128, 3, 4, 2, true, bf16_t>(ga, p.splits, s);
