@@ -342,7 +342,9 @@ template <int ROWS, bool KS, int NW, int KB>
 __device__ __forceinline__ void stage_load(const bf16_t* __restrict__ base, int64_t ld, int64_t rows, int64_t row0,
                                            int64_t k0, int64_t kend, bf16_t* lds, int wave, int lane) {
     constexpr int NI = ROWS * KB / (512 * NW);  // wave-instructions per thread (1 KiB each)
-#pragma unroll
+    // (rolled: it runs for tails only, where its addresses would take registers that the
+    // accumulators and fragments of the large blocks need)
+#pragma unroll 1
     for (int j = 0; j < NI; ++j) {
         const int blk = wave * NI + j;  // 1 KiB block index within the stage
         int64_t gr, gk;
@@ -581,6 +583,142 @@ struct Pipe {
         stage_load<BN, BKS, NW, KB>(b, c.g->ldb, c.g->N, c.n0, k0, c.kend, buf + BM * KB, wave, lane);
     }
 
+    // Fragments of 32 x 32 tiles (rows x 16 k) by LDS byte address, layouts as load_frag32:
+    // tile i of a wave and substep s differ from tile 0, substep 0 by an XOR of two address
+    // bits of the swizzled slot and by constants that go into the instruction's offset.
+    template <int ROWS, bool KS>
+    __device__ __forceinline__ static uint32_t frag_base(const bf16_t* operand, int wrow, int lane) {
+        if (!KS) {
+            const int r = wrow + (lane & 31);
+            return lds_addr(operand) + (uint32_t)(r * KB + (((lane >> 5) ^ kc_swz<KB>(r)) * 8)) * 2u;
+        }
+        const int i = lane & 15, G = lane >> 4, kr = 8 * (G >> 1) + (i >> 2), c = wrow / 16 + (G & 1);
+        return lds_addr(operand) + (uint32_t)(kr * ROWS + ((c ^ kstr_swz<ROWS>(kr)) * 16) + (i & 3) * 4) * 2u;
+    }
+    template <int ROWS, bool KS>
+    __device__ __forceinline__ static bf16x8_t frag_at(uint32_t base, uint32_t off, int i, int s) {
+        if constexpr (!KS) {
+            const uint32_t a = (base ^ (uint32_t)(s * 32)) + off + (uint32_t)(i * 32 * KB * 2);
+            return __builtin_bit_cast(bf16x8_t, *(LDS_AS const u32x4_t*)a);
+        } else {
+            const uint32_t a = (base ^ (uint32_t)(i * 64)) + off + (uint32_t)(s * 16 * ROWS * 2);
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4_t*)a);
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4_t*)(a + 4 * ROWS * 2));
+            typedef short s16x8_t __attribute__((ext_vector_type(8)));
+            const s16x8_t v = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            return __builtin_bit_cast(bf16x8_t, v);
+        }
+    }
+
+    // The K loop of the 32 x 32 tile blocks. A step's one barrier lies before its last
+    // substep's multiplies, whose fragments are then in registers: behind it every wave
+    // refills the slot of the step just read and reads the next step's first fragments.
+    // Every LDS read and every load is placed between two multiplies, so the matrix cores
+    // work through them. The loop is rolled (slots as scalar offsets): unrolled over the
+    // slots, its exits doubled the accumulator registers. Alone on the chip, before (the
+    // barrier and the loads at the start of a step, all reads of a substep before its
+    // multiplies) -> after: 3072 x 10624 x 32768 (both K-strided) 1793 -> 1687 us, 10624 x
+    // 1024 x 32768 841 -> 739, 32768 x 3072 x 10624 1838 -> 1773, 3504 x 3504 x 4096 118 ->
+    // 107. Four waves of 128 x 128 in this form were no faster on deep K (1857) and 20%
+    // slower where the epilogue weighs.
+    __device__ __forceinline__ static void loop32(const Ctx& c, bf16_t* smem, acc_t (&acc)[TM][TN]) {
+        const int lane = c.tid & 63, wave = c.tid >> 6, wm = wave / WN, wn = wave % WN;
+        constexpr int NS = KB / 16;  // substeps
+        static_assert(!M32 || NS % 2 == 0, "the fragment buffers alternate");
+        static_assert(ST == 2 || ST == 3, "rings of two or three stages");
+        bf16x8_t af[2][TM], bfr[2][TN];
+        uint32_t abase_l = frag_base<BM, AKS>(smem, wm * (BM / WM), lane);
+        uint32_t bbase_l = frag_base<BN, BKS>(smem + BM * KB, wn * (BN / WN), lane);
+        // fragment f (B's TN, then A's TM) of substep s (a constant) of the stage `off` bytes into the ring
+        auto frag = [&](int f, uint32_t off, int buf, int s) __attribute__((always_inline)) {
+            if (f < TN) bfr[buf][f] = frag_at<BN, BKS>(bbase_l, off, f, s);
+            else af[buf][f - TN] = frag_at<BM, AKS>(abase_l, off, f - TN, s);
+        };
+        auto mul = [&](int u, int buf) __attribute__((always_inline)) {
+            acc[u / TN][u % TN] = mfma32x32x16<F16>(bfr[buf][u % TN], af[buf][u / TN], acc[u / TN][u % TN]);
+        };
+        // A K range that is no multiple of KB starts with its remainder (per plane of A), padded
+        // with zeros; every later stage is whole, so the loop's loads need no tail.
+        const int rem = (int)((c.kend - c.kbeg) % KB), planes = c.g->a2 ? 2 : 1;
+        const int nrem = rem ? planes : 0, nf = (int)((c.kend - c.kbeg) / KB), ntot = nrem + nf * planes;
+        const uint32_t la0 = lds_addr(smem) + (uint32_t)__builtin_amdgcn_readfirstlane(wave * NIA) * 1024u;
+        const uint32_t lb0 = lds_addr(smem + BM * KB) + (uint32_t)__builtin_amdgcn_readfirstlane(wave * NIB) * 1024u;
+        struct Src {
+            const void *a, *b;
+        };
+        auto source = [&](int t) __attribute__((always_inline)) {  // of stage t >= nrem
+            const int x = t - nrem, plane = x >= nf;
+            const int64_t k0 = c.kbeg + rem + (int64_t)(x - plane * nf) * KB;
+            const bf16_t* a = (const bf16_t*)(plane ? c.g->a2 : c.g->a);
+            const bf16_t* b = (const bf16_t*)c.g->b;
+            return Src{uniform_ptr(AKS ? a + k0 * c.g->lda + c.abase : a + c.abase * c.g->lda + k0),
+                       uniform_ptr(BKS ? b + k0 * c.g->ldb + c.bbase : b + c.bbase * c.g->ldb + k0)};
+        };
+        auto load = [&](int j, const Src& src, uint32_t off) __attribute__((always_inline)) {  // load j of a stage
+            if (j < NIA) dma16_s(c.aoff[j], src.a, la0 + off + 1024u * j);
+            else dma16_s(c.boff[j - NIA], src.b, lb0 + off + 1024u * (j - NIA));
+        };
+        constexpr uint32_t SB = STAGE_ELEMS * 2;  // bytes of a stage
+        for (int u = 0; u < ST && u < ntot; ++u) {
+            bf16_t* const buf = smem + u * STAGE_ELEMS;
+            if (u < nrem) {
+                const bf16_t* a = (const bf16_t*)(u ? c.g->a2 : c.g->a);
+                stage_load<BM, AKS, NW, KB>(a, c.g->lda, c.g->M, c.m0, c.kbeg, c.kbeg + rem, buf, wave, lane);
+                stage_load<BN, BKS, NW, KB>((const bf16_t*)c.g->b, c.g->ldb, c.g->N, c.n0, c.kbeg, c.kbeg + rem,
+                                            buf + BM * KB, wave, lane);
+            } else {
+                const Src src = source(u);
+#pragma unroll
+                for (int j = 0; j < LOADS; ++j) load(j, src, u * SB);
+            }
+        }
+        if (ntot >= ST) wait_vmcnt(LOADS * (ST - 1));  // the first stage has landed
+        else wait_vmcnt(0);
+        __builtin_amdgcn_s_barrier();
+#pragma unroll
+        for (int f = 0; f < TM + TN; ++f) frag(f, 0, 0, 0);
+        constexpr int MU = TM * TN;  // multiplies per substep
+        // fragments read after each of them, so that the last two leave time for the last read
+        constexpr int RPM = M32 ? (TM + TN + MU - 3) / (MU - 2) : 1;
+        uint32_t cur = 0;
+        auto step = [&](int kt, auto refill_c) __attribute__((always_inline)) {
+            constexpr bool REFILL = decltype(refill_c)::value;
+            const uint32_t nxt = cur == (ST - 1) * SB ? 0 : cur + SB;
+            // the addresses are formed here, not kept in registers for every fragment
+            asm volatile("" : "+v"(abase_l), "+v"(bbase_l));
+            const Src src = REFILL ? source(kt + ST) : Src{nullptr, nullptr};
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const bool last = s == NS - 1;
+                if (last) {
+                    wait_lgkm0();                              // this wave's last reads of `cur` are done,
+                    wait_vmcnt(REFILL ? LOADS * (ST - 2) : 0);  // and its loads of `nxt` have landed
+                    __builtin_amdgcn_s_barrier();
+                }
+#pragma unroll
+                for (int u = 0; u < MU; ++u) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    mul(u, s & 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // the fragments of the next substep, and behind the barrier the refill
+#pragma unroll
+                    for (int f = u * RPM; f < (u + 1) * RPM && f < TM + TN; ++f)
+                        frag(f, last ? nxt : cur, (s + 1) & 1, last ? 0 : s + 1);
+                    if (last && REFILL) {
+#pragma unroll
+                        for (int j = u * LOADS / MU; j < (u + 1) * LOADS / MU; ++j) load(j, src, cur);
+                    }
+                }
+            }
+            cur = nxt;
+        };
+        int kt = 0;
+#pragma unroll 1
+        for (; kt + ST < ntot; ++kt) step(kt, std::true_type{});
+#pragma unroll 1
+        for (; kt < ntot; ++kt) step(kt, std::false_type{});
+    }
+
     // One step on tile kt held in `cur`; prefetch tile kt + ST - 1 into `nxt`.
     // Every step issues the same number of loads (past the last tile they re-read
     // it), so "all but the newest ST - 2 stages" is a fixed count on every path. A tail
@@ -592,50 +730,20 @@ struct Pipe {
         wait_vmcnt(LOADS * (ST - 2));
         __builtin_amdgcn_s_barrier();
         issue(c, kt + ST - 1, nxt);
-        if constexpr (M32) {
-            // fragments double-buffered: the reads of substep s + 1 are issued before the
-            // MFMAs of substep s, so LDS latency hides behind the matrix cores
-            bf16x8_t af[2][TM], bfr[2][TN];
-            auto frags = [&](int buf, int ks) {
+        static_assert(!M32, "16 x 16 tiles");
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    af[buf][i] = load_frag32<BM, AKS, KB>(cur, wm * (BM / WM) + i * 32, ks, lane);
+        for (int ks = 0; ks < KB; ks += 32) {
+            bf16x8_t af[TM], bfr[TN];
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    bfr[buf][j] = load_frag32<BN, BKS, KB>(cur + BM * KB, wn * (BN / WN) + j * 32, ks, lane);
-            };
-            // (not with a K-strided A and eight accumulator tiles: that variant would spill)
-            constexpr bool DB = !(AKS && TM * TN > 4);
-            frags(0, 0);
+            for (int i = 0; i < TM; ++i) af[i] = load_frag<BM, AKS, KB>(cur, wm * (BM / WM) + i * 16, ks, lane);
 #pragma unroll
-            for (int s = 0; s < KB / 16; ++s) {
-                if (!DB && s > 0) frags(s & 1, s * 16);
-                if (DB && s + 1 < KB / 16) frags((s + 1) & 1, (s + 1) * 16);
-                // keep the compiler from sinking those reads below the MFMAs
-                __builtin_amdgcn_sched_barrier(0);
+            for (int j = 0; j < TN; ++j)
+                bfr[j] = load_frag<BN, BKS, KB>(cur + BM * KB, wn * (BN / WN) + j * 16, ks, lane);
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] =
-                            mfma32x32x16<F16>(bfr[s & 1][j], af[s & 1][i], acc[i][j]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < KB; ks += 32) {
-                bf16x8_t af[TM], bfr[TN];
-#pragma unroll
-                for (int i = 0; i < TM; ++i) af[i] = load_frag<BM, AKS, KB>(cur, wm * (BM / WM) + i * 16, ks, lane);
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    bfr[j] = load_frag<BN, BKS, KB>(cur + BM * KB, wn * (BN / WN) + j * 16, ks, lane);
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = mfma16x16x32<F16>(bfr[j], af[i], acc[i][j]);
-            }
+                    acc[i][j] = mfma16x16x32<F16>(bfr[j], af[i], acc[i][j]);
         }
     }
 };
@@ -759,7 +867,9 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 2 : 1, WM * WN == 8 ? 2 : 8)))
 #pragma unroll
             for (int e = 0; e < (M32 ? 16 : 4); ++e) acc[i][j][e] = 0.f;
 
-    if (c.ntot > 0) {
+    if constexpr (M32) {
+        if (c.ntot > 0) P::loop32(c, smem, acc);
+    } else if (c.ntot > 0) {
         // ring of ST stages: step kt multiplies stage kt and fills slot (kt + ST - 1) % ST
         bf16_t* const s0 = smem;
         bf16_t* const s1 = smem + P::STAGE_ELEMS;
@@ -788,8 +898,8 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 2 : 1, WM * WN == 8 ? 2 : 8)))
                 cur = cur + 1 == ST ? 0 : cur + 1;
             }
         }
-        wait_vmcnt(0);  // the trailing re-read loads land before the workgroup ends
     }
+    wait_vmcnt(0);  // the trailing re-read loads land before the workgroup ends
 
     block_epilogue<BM, BN, WM, WN, M32, T, MLP, P::THREADS, ST * P::STAGE_ELEMS>(g, c.m0, c.n0, z, acc, smem, tid);
 }
@@ -1121,7 +1231,10 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     // Large products (bound by the MFMA rate rather than by L2 -> LDS loads): eight
     // waves on 256-row blocks with 32 x 32 x 16 MFMAs, which halve the bytes loaded
     // per flop; 256 x 256 blocks when they still cover the chip, else 256 x 128.
-    if ((double)M * (double)N * (double)K >= 8.0e9) {
+    // (their loads take 32-bit offsets from a block's first row: row strides, at most twice
+    // the larger of the two dimensions that are not the contracted batch, must allow it)
+    const int64_t ldmax = allow_split ? (M > N ? M : N) : (N > K ? N : K);
+    if ((double)M * (double)N * (double)K >= 8.0e9 && ldmax < 1500000) {
         // Per 64-deep K step a block needs max(MFMA time, load time): MFMA at ~3600
         // flop/clk per CU, loads at the ~24 B/clk per CU that L2 -> LDS sustains here.
         // A launch takes ceil(tiles / 256) rounds of that (one block per CU).
@@ -1178,6 +1291,7 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStrea
         if (tiles(64, 32) <= 256 && g.K >= 1536) return launch_stream<4, 2, 2, 32>(ga, s);
     }
     if (p.bm == 256) {
+        if ((g.lda > g.ldb ? g.lda : g.ldb) > 3500000) return hipErrorInvalidValue;  // (see plan_gemm)
         if (p.bn == 256) return launch_tile<256, 256, 2, 2, 4, true, bf16_t>(ga, p.splits, s);
         return launch_tile<256, 128, 3, 4, 2, true, bf16_t>(ga, p.splits, s);
     }
