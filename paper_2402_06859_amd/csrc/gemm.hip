@@ -1214,23 +1214,33 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     // re-reads, and recover parallelism by splitting the batch dimension.
     if (t128 >= 240 || (allow_split && M >= 128 && N >= 128)) p.bm = p.bn = 128;
     else p.bm = p.bn = 64;
-    const int64_t tiles = ((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn);
-    p.splits = 1;
-    if (allow_split && tiles < 256) {
+    auto split = [&](int64_t tiles) {
+        if (!allow_split || tiles >= 256) return (int64_t)1;
         int64_t s = (split_blocks + tiles - 1) / tiles;
         const int64_t kmax = K / 512;  // keep >= 8 K steps of 64 per split
         if (s > kmax) s = kmax;
         if (s > 16) s = 16;
-        if (s < 1) s = 1;
-        p.splits = (int)s;
-    }
-    // 128 x 128 tiles: two LDS stages (64 KiB) let two workgroups share a CU, which
-    // overlaps one tile's loads and epilogue with the other's multiplies; this beats
-    // a third stage (one workgroup per CU) at every K measured.
-    p.stages = p.bm == 128 ? 2 : 3;
+        return s < 1 ? (int64_t)1 : s;
+    };
+    int64_t sp = split(t128);
+    // weight gradients of a short batch: 64 x 64 tiles where 128 x 128 ones leave half the
+    // chip idle (1064 x 400 x 1501: 72 blocks 12.9 us, 238 blocks 9.7)
+    if (allow_split && p.bm == 128 && t128 * sp < 128) p.bm = p.bn = 64;
+    if (p.bm == 64) sp = split(((M + 63) / 64) * ((N + 63) / 64));
+    p.splits = (int)sp;
+    // 128 x 128 tiles: two LDS stages (64 KiB) let two workgroups share a CU, which overlaps
+    // one tile's loads and epilogue with the other's multiplies, when there are more than one
+    // per CU; else three stages and 32 x 32 multiplies. us, two stages / three: 4096 x 768 x
+    // 1856 (192 tiles) 27.6 / 22.6, 256 x 1856 x 4096 in 5 splits (150) 17.8 / 14.9, 768 x 1856
+    // x 4096 in 2 (180) 31.3 / 25.2; 4096 x 1856 x 256 (480) 18.3 / 25.1. From 160 tiles on
+    // these beat 64 x 64 ones (the 192 above in the model: 25.0 / 23.5).
+    if (!allow_split && t128 >= 160 && t128 < 240) p.bm = p.bn = 128;
+    p.stages = p.bm == 128 && t128 * sp > 256 ? 2 : 3;
     // Large products (bound by the MFMA rate rather than by L2 -> LDS loads): eight
     // waves on 256-row blocks with 32 x 32 x 16 MFMAs, which halve the bytes loaded
-    // per flop; 256 x 256 blocks when they still cover the chip, else 256 x 128.
+    // per flop; 256 x 256 blocks when they still cover the chip, else 256 x 128 if those
+    // cover more than half of it (8192 x 512 x 4352: 128 blocks of 256 x 128 70 us, 256 of
+    // 128 x 128 53).
     // (their loads take 32-bit offsets from a block's first row: row strides, at most twice
     // the larger of the two dimensions that are not the contracted batch, must allow it)
     const int64_t ldmax = allow_split ? (M > N ? M : N) : (N > K ? N : K);
@@ -1243,6 +1253,19 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
             const double mfma = 2.0 * bm * bn * 64 / 3600.0, load = (bm + bn) * 64 * 2 / 24.0;
             return std::ceil(tiles / 256.0) * (mfma > load ? mfma : load);
         };
+        // Weight gradients of few tiles over a long batch: 256 x 256 blocks that split it until
+        // they fill the chip, if 32 steps or more stay for each (4352 x 512 x 16384, 34 tiles in 7
+        // splits against 136 of 128 x 128 in 3, with the reduction, alone: 95 -> 91 us, transposed
+        // 121 -> 91; feed's backward beside its main stream 3723 -> 3664; with 18 steps each, at
+        // batch 8192, 1% slower).
+        const int64_t tw = ((M + 255) / 256) * ((N + 255) / 256);
+        if (allow_split && tw <= 64 && K / (256 / tw) >= 2048) {
+            p.bm = p.bn = 256;
+            p.splits = (int)(256 / tw > 16 ? 16 : 256 / tw);
+            p.stages = 2;
+            p.group_m = 4;
+            return p;
+        }
         const double c256 = cost(256, 256), c128 = cost(256, 128);
         const int64_t t256 = ((M + 255) / 256) * ((N + 127) / 128);
         // Tiles in groups of four tile rows: the 32 blocks an XCD runs at once then
@@ -1253,7 +1276,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
             p.splits = 1;
             p.stages = 2;
             p.group_m = 4;
-        } else if (t256 >= 128) {
+        } else if (t256 > 128) {
             p.bm = 256;
             p.bn = 128;
             p.splits = 1;
@@ -1297,7 +1320,7 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStrea
     }
     if (p.bm == 128) {
         if (p.stages == 2) return launch_tile<128, 128, 2, 2, 2, false, bf16_t>(ga, p.splits, s);
-        return launch_tile<128, 128, 3, 2, 2, false, bf16_t>(ga, p.splits, s);
+        return launch_tile<128, 128, 3, 2, 2, true, bf16_t>(ga, p.splits, s);
     }
     if (p.stages == 2) return launch_tile<64, 64, 2, 2, 2, false, bf16_t>(ga, p.splits, s);
     return launch_tile<64, 64, 3, 2, 2, false, bf16_t>(ga, p.splits, s);

@@ -1,4 +1,4 @@
-"""Products large enough for the 256 x 256 and 256 x 128 blocks, with rows, columns and a
+"""Products large enough for the 256 x 256, 256 x 128 and 128 x 128 blocks, with rows, columns and a
 contracted dimension that are no multiples of a block or a stage (the remainder of K comes
 first, per plane of A), against float64 products on the same device.
 
@@ -20,7 +20,12 @@ def rel(a, b):
 
 # rows, categorical features x 16 + dense = width, rank (no attention: any rank)
 @pytest.mark.parametrize("mode,tol", [("storage", 1e-2), ("hilo", 5e-3), ("f16", 5e-3)])
-@pytest.mark.parametrize("rows,dense,rank", [(2003, 2088, 2056), (4100, 1032, 2184), (1537, 3080, 1736)])
+@pytest.mark.parametrize("rows,dense,rank", [(2003, 2088, 2056), (4100, 1032, 2184), (1537, 3080, 1736),
+                                             (8300, 1976, 2024),   # weight gradients: 256 x 256, the batch in 4
+                                             (16500, 984, 1016),   # ... in 16: 16 tiles, ragged, uneven splits
+                                             (8100, 2024, 504),    # 256 blocks of 128 x 128, three stages
+                                             (2500, 1080, 1064),   # fewer of them; weight gradients split too
+                                             (1301, 1048, 408)])   # weight gradients on 64 x 64 blocks
 def test_products(rows, dense, rank, mode, tol):
     need_gpu()
     dev = "cuda"
