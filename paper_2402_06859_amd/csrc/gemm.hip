@@ -1234,17 +1234,20 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     // 1856 (192 tiles) 27.6 / 22.6, 256 x 1856 x 4096 in 5 splits (150) 17.8 / 14.9, 768 x 1856
     // x 4096 in 2 (180) 31.3 / 25.2; 4096 x 1856 x 256 (480) 18.3 / 25.1. From 160 tiles on
     // these beat 64 x 64 ones (the 192 above in the model: 25.0 / 23.5).
-    if (!allow_split && t128 >= 160 && t128 < 240) p.bm = p.bn = 128;
-    p.stages = p.bm == 128 && t128 * sp > 256 ? 2 : 3;
+    // (Products of fewer rows than a tile stay on 64 x 64 ones, as half of it would be padding.)
+    if (!allow_split && M >= 128 && N >= 128 && t128 >= 160 && t128 < 240) p.bm = p.bn = 128;
+    // The 32 x 32 multiply loops take 32-bit load offsets from a block's first row: at least 8
+    // rows, and row strides (at most twice the larger of the two dimensions that are not the
+    // contracted batch) that allow it. Other products keep the loop that checks per block.
+    const int64_t ldmax = allow_split ? (M > N ? M : N) : (N > K ? N : K);
+    const bool offsets32 = M >= 8 && N >= 8 && ldmax < 1500000;
+    p.stages = p.bm == 128 && (t128 * sp > 256 || !offsets32) ? 2 : 3;
     // Large products (bound by the MFMA rate rather than by L2 -> LDS loads): eight
     // waves on 256-row blocks with 32 x 32 x 16 MFMAs, which halve the bytes loaded
     // per flop; 256 x 256 blocks when they still cover the chip, else 256 x 128 if those
     // cover more than half of it (8192 x 512 x 4352: 128 blocks of 256 x 128 70 us, 256 of
     // 128 x 128 53).
-    // (their loads take 32-bit offsets from a block's first row: row strides, at most twice
-    // the larger of the two dimensions that are not the contracted batch, must allow it)
-    const int64_t ldmax = allow_split ? (M > N ? M : N) : (N > K ? N : K);
-    if ((double)M * (double)N * (double)K >= 8.0e9 && ldmax < 1500000) {
+    if ((double)M * (double)N * (double)K >= 8.0e9 && offsets32) {
         // Per 64-deep K step a block needs max(MFMA time, load time): MFMA at ~3600
         // flop/clk per CU, loads at the ~24 B/clk per CU that L2 -> LDS sustains here.
         // A launch takes ceil(tiles / 256) rounds of that (one block per CU).
@@ -1313,8 +1316,11 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStrea
         if (tiles(32, 32) <= 256) return launch_stream<2, 2, 2, 64>(ga, s);
         if (tiles(64, 32) <= 256 && g.K >= 1536) return launch_stream<4, 2, 2, 32>(ga, s);
     }
+    // the 32 x 32 multiply loops' offsets (see plan_gemm)
+    if ((p.bm == 256 || (p.bm == 128 && p.stages == 3)) &&
+        (g.M < 8 || g.N < 8 || (g.lda > g.ldb ? g.lda : g.ldb) > 3500000))
+        return hipErrorInvalidValue;
     if (p.bm == 256) {
-        if ((g.lda > g.ldb ? g.lda : g.ldb) > 3500000) return hipErrorInvalidValue;  // (see plan_gemm)
         if (p.bn == 256) return launch_tile<256, 256, 2, 2, 4, true, bf16_t>(ga, p.splits, s);
         return launch_tile<256, 128, 3, 4, 2, true, bf16_t>(ga, p.splits, s);
     }

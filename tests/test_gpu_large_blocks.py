@@ -25,7 +25,9 @@ def rel(a, b):
                                              (16500, 984, 1016),   # ... in 16: 16 tiles, ragged, uneven splits
                                              (8100, 2024, 504),    # 256 blocks of 128 x 128, three stages
                                              (2500, 1080, 1064),   # fewer of them; weight gradients split too
-                                             (1301, 1048, 408)])   # weight gradients on 64 x 64 blocks
+                                             (1301, 1048, 408),    # weight gradients on 64 x 64 blocks
+                                             # fewer rows than a load's clamp, over many column tiles
+                                             (5, 20488, 64), (5, 30984, 64)])
 def test_products(rows, dense, rank, mode, tol):
     need_gpu()
     dev = "cuda"
