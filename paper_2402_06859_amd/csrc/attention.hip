@@ -275,6 +275,29 @@ __device__ __forceinline__ u32x4_t pack_e(const float (&e)[8]) {
     return u32x4_t{pk_f16(e[0], e[1]), pk_f16(e[2], e[3]), pk_f16(e[4], e[5]), pk_f16(e[6], e[7])};
 }
 
+// -1 where the compiler cannot fold it: x - h for an f16 h is then one mixed-precision FMA that
+// rounds to f16, where a subtraction converts h, subtracts and converts back.
+__device__ __forceinline__ float minus_one() {
+    float m = -1.f;
+    asm("" : "+s"(m));
+    return m;
+}
+// A packed f16 pair or fragment as it is stored: what is computed from it reads these bits (the
+// compiler would otherwise round the floats again, an unrounded product among them).
+template <typename V>
+__device__ __forceinline__ V as_stored(V x) {
+    asm("" : "+v"(x));
+    return x;
+}
+// What pack_e's rounding leaves of each e, as f16.
+__device__ __forceinline__ u32x4_t pack_e_lo(const float (&e)[8], const u32x4_t& hi, float m1) {
+    const f16x8_t h = __builtin_bit_cast(f16x8_t, hi);
+    f16x8_t l;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) l[t] = (_Float16)fmaf((float)h[t], m1, e[t]);
+    return __builtin_bit_cast(u32x4_t, l);
+}
+
 // e for one row (c, m) and the lane's 8 keys kv[0..7] (in the order above),
 // exponent arguments by FMA.
 __device__ __forceinline__ u32x4_t efrag(float c, float m, const float* kv) {
@@ -467,25 +490,36 @@ __device__ __forceinline__ f16x8_t frag32(const _Float16* sx, int ld, int lane, 
 // and a key's sums values of functions of s. The range [-Y, Y] of y (of s: [-1, 1]) is cut
 // into n panels of half width h <= rho (Y / n for s); inside the panel at y_p
 //   2^(y s) = 2^(y_p s) e^(x s),   x = (y - y_p) ln 2,  |x s| <= rho ln 2,
-// and e^t is a polynomial of degree 7 (relative error 5e-7, its derivative's 5e-6, against the
-// 2.4e-4 of one exponential rounded to f16). So one exponential per (panel, key) is enough:
+// and e^t is a polynomial of degree 7 (relative error 5e-7 and its derivative's 5e-6 on the forward's
+// panels, 2.5e-6 on the backward's wider ones). So one exponential per (panel, key) is enough:
 // the moments sum_j w_j s_j^t 2^(y_p s_j - |y_p|), t = 0 .. 7, run on the matrix cores (A
 // operand: the w s^t as f16 hi + lo pairs; B operand: the exponentials, 16 panels x 32 keys
 // per v_mfma_f32_16x16x32_f16), and each row evaluates its panel's polynomials and their
 // derivatives by Horner's rule in float. n = 16 ceil(Y / 24) (/ 32 in the backward, which
 // needs no derivative) is 16 to 48 for the scores of a freshly drawn layer (|logits| up to
-// 30 or so) and about 100 when they reach 130, against r = 256 .. 1024 exponentials per row
-// for the direct sums; those stay for samples whose scores need more than 3 r / 8 (r / 4)
-// panels or exceed the f16 range, and for small ranks.
+// 30 or so) and 128 (96 in the backward) when they reach 130, against r = 256 .. 1024
+// exponentials per row for the direct sums; those stay for samples whose scores need more than
+// 3 r / 8 (r / 4) panels or exceed the f16 range, and for small ranks.
+// The exponentials too are f16 hi + lo pairs. The direct sums round them once, but Z, o and the
+// backward's sums of a row share the rounded values, so that most of the error leaves with the
+// division by Z; panels of rows and panels of keys round different exponentials, and with one f16
+// each the backward's sums were 1.5 to 4 times further from float64 than the direct ones (rank 512,
+// spread 9: gk 5.0e-4 against 2.8e-4, gv 6.8e-4 against 9.7e-5). With pairs in both directions they
+// are within 2e-5 at ranks 136 to 1024, spreads 0.3 to 9 (pairs in the backward alone leave the
+// error of Z and o in gk: 6.4e-4 against 3.8e-4 at rank 1024, spread 9).
 // Measured (direct -> panel sums, us per launch alone, |logits| up to 30): batch 8192, rank
-// 1024: forward 713 -> 86, backward 732 -> 130; batch 4096, rank 512: 105 -> 28, 108 -> 44;
-// batch 4096, rank 256: 37 -> 19, 39 -> 22; with ten times the logits, rank 1024: 709 -> 236,
-// 728 -> 302. What remains is bound by the vector work around the exponentials (the tiles'
-// powers, the polynomials) and the traffic of [v|q|k], h and the statistics. Where a line
-// between the two forms lies: a panel costs what about r / 2.7 (forward) or r / 4 (backward)
-// direct exponentials per row cost (rank 256: 0.22 and 0.3 us per panel at batch 4096), and
-// below ranks 128 and 192 the direct sums take no longer than the panels' set-up (rank 128,
-// batch 8192: forward 24 -> 16, backward 25 -> 24 us; rank 64: 12.5 -> 13.7, 13 -> 21).
+// 1024: forward 723 -> 102, backward 742 -> 147; batch 4096, rank 512: 106 -> 32, 109 -> 48;
+// batch 4096, rank 256: 32 -> 17, 32 -> 20; with ten times the logits, rank 1024: 723 -> 491,
+// 743 -> 571. (One f16 per exponential: 94, 139; 29, 46; 16, 19; 399, 510.) What remains is bound by
+// the vector work around the exponentials (the tiles' powers, the polynomials) and the traffic of
+// [v|q|k], h and the statistics. Where a line between the two forms lies: a panel costs what 2
+// (forward) or 3.2 (backward) of a row's r direct exponentials cost (rank 256, batch 4096: 0.25 and
+// 0.4 us against 0.126), on top of the set-up, and below ranks 128 and 192 the direct sums
+// take no longer than the panels' set-up (rank 128, batch 8192: forward 23 -> 16.5; rank 64, panels
+// forced: 12.5 -> 13.7, 13 -> 21). A sample beyond the line pays for the choice and for the
+// panel kernels' registers and LDS: against kernels of the direct sums alone, |logits| of 500 and more,
+// rank 1024 726 -> 759 and 748 -> 780, rank 512 113 -> 115 and 110 -> 126, rank 256 32.3 -> 35.7 and
+// 32.1 -> 35.1 us.
 //
 // Data are handled in tiles of 128 entries, two consecutive entries per lane. A tile's
 // operand matrix is kept in LDS as chunks of 8 entries x 16 rows (16 bytes per row and
@@ -543,12 +577,15 @@ __device__ __forceinline__ int panel_of(const Panels& p, float y, float Y) {
 // Rows row .. row + 7 of a tile's hi and lo matrices: w z^t of entries 2 lane, 2 lane + 1.
 __device__ __forceinline__ void put_powers(_Float16* hi, _Float16* lo, int row, int lane, float2 w, float2 z) {
     const int off = (lane >> 2) * AP_PITCH + ((2 * lane) & 7) + row * 8;
+    const float m1 = minus_one();
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-        const uint32_t h = pk_f16(w.x, w.y);
+        w = make_float2(as_stored(w.x), as_stored(w.y));  // the float product: the pair is its hi and lo part
+        const uint32_t h = as_stored(pk_f16(w.x, w.y));
         const f16x2_t hv = __builtin_bit_cast(f16x2_t, h);
+        const f16x2_t lv = {(_Float16)fmaf((float)hv.x, m1, w.x), (_Float16)fmaf((float)hv.y, m1, w.y)};
         *(uint32_t*)(hi + off + 8 * t) = h;
-        *(uint32_t*)(lo + off + 8 * t) = pk_f16(w.x - (float)hv.x, w.y - (float)hv.y);
+        *(uint32_t*)(lo + off + 8 * t) = __builtin_bit_cast(uint32_t, lv);
         w.x *= z.x;
         w.y *= z.y;
     }
@@ -688,6 +725,7 @@ __device__ __forceinline__ void attn_fwd_panels(const ScoreRange& R, int r, floa
     const float vs = pow2_ceil(vmax), ivs = 1.0f / vs;  // exact scaling: a power of two
     const float cq = LOG2E * inv_tau * R.Hk;
     const int ng = R.p.n / 16, col = lane & 15;
+    const float m1 = minus_one();
     float2 ov[TPW], zv[TPW], dv[TPW];
 #pragma unroll
     for (int i = 0; i < TPW; ++i) ov[i] = zv[i] = dv[i] = make_float2(0.f, 0.f);
@@ -725,9 +763,12 @@ __device__ __forceinline__ void attn_fwd_panels(const ScoreRange& R, int r, floa
                             float e[8];
 #pragma unroll
                             for (int u = 0; u < 8; ++u) e[u] = __builtin_amdgcn_exp2f(fmaf(yp[g], s8[u], -fabsf(yp[g])));
-                            const f16x8_t ef = __builtin_bit_cast(f16x8_t, pack_e(e));
+                            const u32x4_t ep = as_stored(pack_e(e));
+                            const f16x8_t ef = __builtin_bit_cast(f16x8_t, ep),
+                                          el = __builtin_bit_cast(f16x8_t, pack_e_lo(e, ep, m1));
                             acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, ef, acc[g], 0, 0, 0);
                             acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, ef, acc[g], 0, 0, 0);
+                            acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, el, acc[g], 0, 0, 0);
                         }
                 }
             }
@@ -1061,6 +1102,7 @@ __device__ __forceinline__ void attn_bwd_panels(const ScoreRange& R, int r, floa
     const float iY = R.Y > 1e-20f ? 1.f / R.Y : 0.f, xs = R.Y * LN2;
     const int n = R.p.n, ng = n / 16, col = lane & 15;
     const float sh = 1.f / (float)n;  // half width of a panel of s
+    const float m1 = minus_one();
     float2 c1[TPW], c3[TPW];  // dk, dv of the wave's keys
 #pragma unroll
     for (int i = 0; i < TPW; ++i) c1[i] = c3[i] = make_float2(0.f, 0.f);
@@ -1098,10 +1140,14 @@ __device__ __forceinline__ void attn_bwd_panels(const ScoreRange& R, int r, floa
                             float e[8];
 #pragma unroll
                             for (int u = 0; u < 8; ++u) e[u] = __builtin_amdgcn_exp2f(fmaf(sp[g], y8[u], -fabsf(y8[u])));
-                            const f16x8_t ef = __builtin_bit_cast(f16x8_t, pack_e(e));
+                            const u32x4_t ep = as_stored(pack_e(e));
+                            const f16x8_t ef = __builtin_bit_cast(f16x8_t, ep),
+                                          el = __builtin_bit_cast(f16x8_t, pack_e_lo(e, ep, m1));
                             acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, ef, acc[g], 0, 0, 0);
                             acg[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ag, ef, acg[g], 0, 0, 0);
                             acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, ef, acc[g], 0, 0, 0);
+                            acg[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ag, el, acg[g], 0, 0, 0);
+                            acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, el, acc[g], 0, 0, 0);
                         }
                 }
             }

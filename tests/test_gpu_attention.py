@@ -15,6 +15,7 @@ import torch
 
 import oracle
 from gpu_helpers import need_gpu, relerr, to_np
+from paper_2402_06859_amd.rdcn import Rdcn, make_config
 from paper_2402_06859_amd.step import DeviceBatch
 from paper_2402_06859_amd.synth import Workload, make_inputs
 
@@ -93,3 +94,48 @@ def test_degenerate_ranges(rank, what):
             w[rank:, 64:] += 0.08
 
     compare(Workload("att_deg", 22, 5, 4, 20_000, 150, 16, 64, 1, rank, True, "bf16", "sum", 1.1), edit)
+
+
+# 192 and 256: one wave per sample; 264, 520 and 1024: four; spread: of the logits (16 to 96 panels)
+@pytest.mark.parametrize("rank,spread", [(192, 1.0), (256, 0.3), (256, 3.0), (264, 1.0), (512, 3.0), (520, 1.0),
+                                         (1024, 1.0)])
+def test_panel_sums_precision(rank, spread):
+    """The panel sums' error before [gv|gq|gk] are stored as bf16. Sample b of x0 is the unit
+    vector e_b, so that its v, q, k are column b of W and its gh row b of U, exactly, and
+    column b of W's gradient holds its stored [gv|gq|gk]; skip_beta is 0, so that gv is the
+    softmax's sum alone. How many stored values are not the float64 value's bf16 measures
+    the error: one relative to a value of eps flips a share of about eps / 2^-7.5 (the spacing).
+    Rounding the exponentials to f16 (2^-11) in every sum, as the direct form does, flips
+    3 to 10% (the same sums evaluated in float64 with that one rounding); float sums of hi +
+    lo pairs below 1% on average. Bar: 1%."""
+    need_gpu()
+    dev, B, d = "cuda", 8, 64
+    g = torch.Generator(device=dev)
+    g.manual_seed(rank)
+    rand = lambda *s: torch.randn(*s, device=dev, generator=g)
+    W = rand(3 * rank, d)
+    W[rank:2 * rank] *= spread
+    W, U, b = W.bfloat16(), rand(d, rank).bfloat16(), torch.zeros(d, dtype=torch.bfloat16, device=dev)
+    x0 = torch.zeros(B, d, dtype=torch.bfloat16, device=dev)
+    x0[range(B), range(B)] = 1
+    lib = Rdcn(make_config(B, 1, 16, d - 16, rank, 1, 40, 40, 1600, attn_alpha=1.0, skip_beta=0.0))
+    saved, scratch = (torch.empty(n, dtype=torch.uint8, device=dev) for n in lib.workspace_bytes(B))
+    x_out, gx0 = torch.empty_like(x0), torch.empty(B, d, device=dev)
+    gW, gU, gb = (torch.empty(t.shape, device=dev) for t in (W, U, b))
+    lib.rdcn_forward(B, x0, [W], [U], [b], x_out, saved, scratch)
+    lib.rdcn_backward(B, x0, [W], [U], [b], saved, torch.ones_like(x0), gx0, [gW], [gU], [gb], scratch)
+    torch.cuda.synchronize()
+    v, q, k = (W[i * rank:(i + 1) * rank, :B].double().t()[:, None, :] for i in range(3))  # [B, 1, r]
+    go, q = U[:B].double()[:, :, None], q.transpose(1, 2)                                  # [B, r, 1]
+    A = torch.softmax(q * k, 2)
+    D = A * (v - (A * v).sum(2, keepdim=True))
+    ref = torch.cat([(A * go).sum(1), (go * D * k).sum(2), (D * go * q).sum(1)], 1).t()    # [3 r, B]
+    got = gW[:, :B].double()
+    assert torch.equal(got, got.bfloat16().double())
+    shares = []
+    for i in range(3):
+        y, x = ref[i * rank:(i + 1) * rank], got[i * rank:(i + 1) * rank]
+        big = y.abs() >= 0.25 * y.square().mean(0, keepdim=True).sqrt()
+        shares.append(float((y.float().bfloat16().double() != x)[big].double().mean()))
+    print(rank, spread, "flipped roundings gv %.4f gq %.4f gk %.4f" % tuple(shares), flush=True)
+    assert sum(shares) / 3 <= 0.01
