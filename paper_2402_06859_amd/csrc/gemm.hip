@@ -338,13 +338,17 @@ __device__ __align__(16) const uint32_t kZero16[4] = {0u, 0u, 0u, 0u};
 // Rows past `rows` re-read the last row (their results are discarded); K positions at
 // or past kend read zeros. K-contiguous operands need kend - k0 to be a multiple of 8
 // (a 16-byte piece never straddles kend: K is a multiple of 8 for bf16 models).
-template <int ROWS, bool KS, int NW, int KB>
+// ROLLED keeps its addresses out of the registers, for the 32 x 32 loop, whose accumulators and
+// fragments need them and which loads one remainder per block with it. The other loops load
+// their partial last stage, its re-reads and, without 32-bit offsets (under 8 rows), every
+// stage with it: unrolled, the address arithmetic of its loads overlaps (the Feed head's training
+// pass at batches 200 to 600, rolled -> unrolled: 420 -> 408 to 674 -> 661 us; requests of 1 to 7 rows
+// at width 13824 or 10624: 74 -> 67 to 72 -> 70).
+template <int ROWS, bool KS, int NW, int KB, bool ROLLED = false>
 __device__ __forceinline__ void stage_load(const bf16_t* __restrict__ base, int64_t ld, int64_t rows, int64_t row0,
                                            int64_t k0, int64_t kend, bf16_t* lds, int wave, int lane) {
     constexpr int NI = ROWS * KB / (512 * NW);  // wave-instructions per thread (1 KiB each)
-    // (rolled: it runs for tails only, where its addresses would take registers that the
-    // accumulators and fragments of the large blocks need)
-#pragma unroll 1
+#pragma unroll(ROLLED ? 1 : NI)
     for (int j = 0; j < NI; ++j) {
         const int blk = wave * NI + j;  // 1 KiB block index within the stage
         int64_t gr, gk;
@@ -663,9 +667,9 @@ struct Pipe {
             bf16_t* const buf = smem + u * STAGE_ELEMS;
             if (u < nrem) {
                 const bf16_t* a = (const bf16_t*)(u ? c.g->a2 : c.g->a);
-                stage_load<BM, AKS, NW, KB>(a, c.g->lda, c.g->M, c.m0, c.kbeg, c.kbeg + rem, buf, wave, lane);
-                stage_load<BN, BKS, NW, KB>((const bf16_t*)c.g->b, c.g->ldb, c.g->N, c.n0, c.kbeg, c.kbeg + rem,
-                                            buf + BM * KB, wave, lane);
+                stage_load<BM, AKS, NW, KB, true>(a, c.g->lda, c.g->M, c.m0, c.kbeg, c.kbeg + rem, buf, wave, lane);
+                stage_load<BN, BKS, NW, KB, true>((const bf16_t*)c.g->b, c.g->ldb, c.g->N, c.n0, c.kbeg, c.kbeg + rem,
+                                                  buf + BM * KB, wave, lane);
             } else {
                 const Src src = source(u);
 #pragma unroll

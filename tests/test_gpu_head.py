@@ -154,6 +154,17 @@ def test_large_mlp_full_batch_sampled():
         assert not np.any(gW[n:]) and not np.any(to_np(dh.grads["b"][l])[n:])
 
 
+# weight gradients whose K loop over the batch is two to seven stages of 64 with a partial last one,
+# at the Feed head's width (128 x 128 blocks), and one short of a whole stage
+@pytest.mark.parametrize("B", [77, 301, 447])
+def test_wide_layers_short_batches(B):
+    need_gpu()
+    wl = WORKLOADS["feed"].with_(batch=B, num_cat=20)
+    head = HeadSpec("wide", (3504, 3504))
+    dh, ref, rows, _ = run_head(wl, head, B, rows=sample_rows(B, 16))
+    compare(dh, ref, rows, gated=True)
+
+
 @pytest.mark.parametrize("case", ["ragged_gated", "ragged_plain", "lmlp"])
 def test_head_against_plain_float64_definition(case):
     """The device against the head computed in float64 from the same bf16 parameters and
