@@ -693,7 +693,7 @@ rdcn_status rdcn_forward(rdcn_handle* h, int64_t batch, const void* x0, const rd
         u.t_out = sv + S.T[l]; u.ldx = d;
         {
             ProfScope ps(h, RDCN_KERNEL_FWD_UP_GEMM, s);
-            RDCN_TRY(launch_gemm(u, plan_gemm(B, d, hr, h->bf16, false), h->bf16, s));
+            RDCN_TRY(launch_gemm(u, plan_gemm(B, d, hr, h->bf16, false, 0, true), h->bf16, s));
         }
         xcur = xnext;
         xcur2 = h->split ? u.c2 : nullptr;
@@ -848,7 +848,7 @@ rdcn_status rdcn_backward(rdcn_handle* h, int64_t batch, const void* x0, const r
             g4.epi = l == 0 ? EPI_RESID_X0 : EPI_RESID;
             g4.c = l == 0 ? (void*)grad_x0 : (void*)g; g4.ldc = d;
             ProfScope ps(h, RDCN_KERNEL_BWD_GX_GEMM, s);
-            RDCN_TRY(launch_gemm(g4, plan_gemm(B, d, nr, h->bf16, false), h->bf16, s));
+            RDCN_TRY(launch_gemm(g4, plan_gemm(B, d, nr, h->bf16, false, 0, true), h->bf16, s));
         }
     }
     // join: the side stream's last work (layer 0) completes before anything later on `s`

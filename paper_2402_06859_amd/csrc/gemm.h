@@ -78,8 +78,10 @@ struct GemmPlan {
 
 // split_blocks: with split-K allowed, the workgroup count the K split aims for when
 // the output tiles alone are fewer than 256 (a product that runs beside other
-// kernels does better with fewer, longer splits).
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split, int split_blocks = 384);
+// kernels does better with fewer, longer splits). fused_out: the epilogue reads and writes 10
+// bytes or more per output (the cross layer's and the residual gradient's).
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split, int split_blocks = 384,
+                   bool fused_out = false);
 hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStream_t s);
 // Column tiles of an MLP GEMM under plan p (the rowpart partials per row).
 inline int64_t gemm_tiles_n(int64_t N, const GemmPlan& p) { return (N + p.bn - 1) / p.bn; }

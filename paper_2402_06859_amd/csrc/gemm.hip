@@ -1199,7 +1199,7 @@ hipError_t launch_tile(const GemmArgs& g, int splits, hipStream_t s) {
 
 }  // namespace
 
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split, int split_blocks) {
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split, int split_blocks, bool fused_out) {
     GemmPlan p;
     if (!bf16) {
         // 64 x 64 blocks (two groups of waves along k) once they fill half the chip, else
@@ -1232,19 +1232,31 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     if (allow_split && p.bm == 128 && t128 * sp < 128) p.bm = p.bn = 64;
     if (p.bm == 64) sp = split(((M + 63) / 64) * ((N + 63) / 64));
     p.splits = (int)sp;
-    // 128 x 128 tiles: two LDS stages (64 KiB) let two workgroups share a CU, which overlaps
-    // one tile's loads and epilogue with the other's multiplies, when there are more than one
-    // per CU; else three stages and 32 x 32 multiplies. us, two stages / three: 4096 x 768 x
-    // 1856 (192 tiles) 27.6 / 22.6, 256 x 1856 x 4096 in 5 splits (150) 17.8 / 14.9, 768 x 1856
-    // x 4096 in 2 (180) 31.3 / 25.2; 4096 x 1856 x 256 (480) 18.3 / 25.1. From 160 tiles on
-    // these beat 64 x 64 ones (the 192 above in the model: 25.0 / 23.5).
+    // 160 to 239 tiles of 128 x 128 run as one round of one block per CU, with three stages and 32 x 32
+    // multiplies; the 64 x 64 blocks (three per CU) overlap their prologues and epilogues, but need
+    // a second round past 192 tiles. So the large tiles pay on a K long enough to make up for the
+    // one exposed epilogue. us, 128 x 128 / 64 x 64:
+    //   plain stores, 4096 x 768 (192 tiles): K 512 10.7 / 10.2, 1024 14.3 / 15.4, 1856 21.1 / 22.8;
+    //     4096 x 640 (160): 1024 14.0 / 14.4, 4352 39 / 43; 5120 x 640 (200): 512 10.6 / 12.9;
+    //     300 x 8832 (207): 512 11.0 / 11.2
+    //   fused_out, 4096 x 640 (160): K 256 12.2 / 10.0, 2048 26.5 / 24.5; 4096 x 768 (192): 256 12.4 / 10.3,
+    //     2048 26.7 / 26.3; 1792 x 1792 (196): 256 13.9 / 13.2, 512 15.7 / 15.9, 1024 19.6 / 21.5, 2048 26.7 /
+    //     33.4; 300 x 8832 (207): 512 16.0 / 14.1, 1024 20.0 / 19.9, 2048 28.0 / 32.5
     // (Products of fewer rows than a tile stay on 64 x 64 ones, as half of it would be padding.)
-    if (!allow_split && M >= 128 && N >= 128 && t128 >= 160 && t128 < 240) p.bm = p.bn = 128;
+    if (!allow_split && M >= 128 && N >= 128 && t128 >= 160 && t128 < 240 &&
+        (fused_out ? t128 > 192 && K >= 1024 : K >= (t128 > 192 ? 512 : 1024)))
+        p.bm = p.bn = 128;
     // The 32 x 32 multiply loops take 32-bit load offsets from a block's first row: at least 8
     // rows, and row strides (at most twice the larger of the two dimensions that are not the
     // contracted batch) that allow it. Other products keep the loop that checks per block.
     const int64_t ldmax = allow_split ? (M > N ? M : N) : (N > K ? N : K);
     const bool offsets32 = M >= 8 && N >= 8 && ldmax < 1500000;
+    // 128 x 128 tiles: two LDS stages (64 KiB) let two workgroups share a CU, which overlaps
+    // one tile's loads and epilogue with the other's multiplies, when there are more than one
+    // per CU; else three stages and 32 x 32 multiplies. us, two stages / three: 4096 x 768 x
+    // 1856 (192 tiles) 27.6 / 22.6, 256 x 1856 x 4096 in 5 splits (150) 15.7 / 13.9, 768 x 1856
+    // x 4096 in 2 (180) 31.3 / 25.2; short K: 4352 x 512 (136) over 130 rows 9.1 / 8.4, over 512 11.8 /
+    // 10.7, over 2000 27.7 / 22.7, 8192 x 512 x 128 (256) 11.8 / 11.8; 4096 x 1856 x 256 (480) 18.3 / 25.1.
     p.stages = p.bm == 128 && (t128 * sp > 256 || !offsets32) ? 2 : 3;
     // Large products (bound by the MFMA rate rather than by L2 -> LDS loads): eight
     // waves on 256-row blocks with 32 x 32 x 16 MFMAs, which halve the bytes loaded

@@ -1,9 +1,12 @@
 """Shared helpers of the GPU parity tests (test infrastructure)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
+from paper_2402_06859_amd import rdcn
 from paper_2402_06859_amd.synth import Workload
 
 
@@ -107,3 +110,18 @@ def sample_rows(B: int, k: int) -> np.ndarray:
 
 FWD_TOL = {"f32": 1e-5, "bf16": 2e-2}
 GRAD_TOL = 5e-2
+
+
+class GemmPlan(ctypes.Structure):
+    """GemmPlan of csrc/gemm.h."""
+    _fields_ = [(k, ctypes.c_int) for k in ("bm", "bn", "splits", "stages", "group_m")]
+
+
+def gemm_plan(M, N, K, dtype="bf16", weight_grad=False, fused_out=False) -> GemmPlan:
+    """The plan the library makes for a product (rdcn::plan_gemm; needs no GPU). weight_grad: one of the
+    cross stack's, with the split target its backward passes."""
+    fn = rdcn.load()._ZN4rdcn9plan_gemmElllbbib
+    fn.restype = GemmPlan
+    fn.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_bool] * 2 + [ctypes.c_int, ctypes.c_bool]
+    blocks = (128 if float(M) * N * K < 8.0e9 else 384) if weight_grad else 0
+    return fn(M, N, K, dtype == "bf16", weight_grad, blocks, fused_out)
