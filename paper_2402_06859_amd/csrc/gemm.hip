@@ -1272,15 +1272,19 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
             const double mfma = 2.0 * bm * bn * 64 / 3600.0, load = (bm + bn) * 64 * 2 / 24.0;
             return std::ceil(tiles / 256.0) * (mfma > load ? mfma : load);
         };
-        // Weight gradients of few tiles over a long batch: 256 x 256 blocks that split it until
-        // they fill the chip, if 32 steps or more stay for each (4352 x 512 x 16384, 34 tiles in 7
-        // splits against 136 of 128 x 128 in 3, with the reduction, alone: 95 -> 91 us, transposed
-        // 121 -> 91; feed's backward beside its main stream 3723 -> 3664; with 18 steps each, at
-        // batch 8192, 1% slower).
+        // Weight gradients of few tiles over a long batch: 256 x 256 blocks in up to 16 splits of it,
+        // if those make 128 blocks or more and 32 steps or more stay for each of a chip's worth of
+        // blocks. gU and gW with their reductions, alone, against 128 x 128 blocks: 4352 x 512 over
+        // 16384 (34 tiles in 7) 226 -> 192 us, over 32768 409 -> 303; 3072 x 768 over 16384 (36 in 7) 251 ->
+        // 191; 1024 x 1024 over 32768 (16 in 16) 249 -> 181. 1856 x 256 over 65536 (8 in 16: 128 blocks) 236 ->
+        // 249, but beside the main stream, which has the other half of the chip, 1200 -> 1153 for
+        // the whole pass, and 1024 x 512 891 -> 812. Fewer blocks leave the chip idle: 512 x 256 over
+        // 262144 (2 in 16) 376 -> 804, the pass 1411 -> 1742.
         const int64_t tw = ((M + 255) / 256) * ((N + 255) / 256);
-        if (allow_split && tw <= 64 && K / (256 / tw) >= 2048) {
+        const int64_t fill = tw <= 64 ? 256 / tw : 1, sw = fill > 16 ? 16 : fill;
+        if (allow_split && tw <= 64 && tw * sw >= 128 && K / fill >= 2048) {
             p.bm = p.bn = 256;
-            p.splits = (int)(256 / tw > 16 ? 16 : 256 / tw);
+            p.splits = (int)sw;
             p.stages = 2;
             p.group_m = 4;
             return p;

@@ -21,3 +21,20 @@ def test_mid_size_products(M, N, K, fused, bm):
     assert (p.bm, p.bn, p.splits) == (bm, bm, 1), (p.bm, p.bn, p.splits)
     # 128 x 128 blocks of at most one per CU run three stages
     assert p.stages == 3
+
+
+# rows of the batch, then width and rank of the gradient: 256 x 256 blocks that split the batch
+@pytest.mark.parametrize("K,M,N,splits", [
+    (8300, 1992, 2024, 4), (16384, 4352, 512, 7), (20500, 1528, 1000, 10), (32767, 1000, 1016, 0), (33000, 1000, 1016, 16),
+    (65536, 1856, 256, 16), (65535, 1856, 256, 0),
+    # fewer than 8 tiles: 16 splits of them would leave more than half of the chip idle
+    (300_000, 1792, 256, 0), (600_000, 256, 256, 0), (131_072, 1024, 256, 0)])
+def test_split_weight_gradients(K, M, N, splits):
+    p = gemm_plan(M, N, K, weight_grad=True)
+    blocks = tiles(M, N, p.bm, p.bn) * p.splits
+    if splits:
+        assert (p.bm, p.bn, p.splits) == (256, 256, splits)
+        assert blocks >= 128
+    else:
+        assert p.bm < 256 and p.splits > 1 and blocks >= 128
+    assert -(-K // p.splits) >= 512
