@@ -8,7 +8,7 @@ lo pairs and f16 (5e-3; x_out itself is bf16). bf16 gradients carry the rounding
 import pytest
 import torch
 
-from gpu_helpers import need_gpu
+from gpu_helpers import gemm_plan, need_gpu
 from paper_2402_06859_amd.rdcn import Rdcn, make_config
 
 pytestmark = pytest.mark.gpu
@@ -18,17 +18,29 @@ def rel(a, b):
     return float((a.double() - b).norm() / b.norm())
 
 
-# rows, categorical features x 16 + dense = width, rank (no attention: any rank)
+# rows, dense inputs (16 more make the width), rank (no attention: any rank); the plans, as (tile rows,
+# tile columns, splits, stages), of the down and up products and of the weight gradients
+B256, B128, M3, M2, S64 = (256, 256, 1, 2), (256, 128, 1, 3), (128, 128, 1, 3), (128, 128, 1, 2), (64, 64, 1, 3)
+
+
 @pytest.mark.parametrize("mode,tol", [("storage", 1e-2), ("hilo", 5e-3), ("f16", 5e-3)])
-@pytest.mark.parametrize("rows,dense,rank", [(2003, 2088, 2056), (4100, 1032, 2184), (1537, 3080, 1736),
-                                             (8300, 1976, 2024),   # weight gradients: 256 x 256, the batch in 4
-                                             (16500, 984, 1016),   # ... in 16: 16 tiles, ragged, uneven splits
-                                             (8100, 2024, 504),    # 256 blocks of 128 x 128, three stages
-                                             (2500, 1080, 1064),   # fewer of them; weight gradients split too
-                                             (1301, 1048, 408),    # weight gradients on 64 x 64 blocks
-                                             # fewer rows than a load's clamp, over many column tiles
-                                             (5, 20488, 64), (5, 30984, 64)])
-def test_products(rows, dense, rank, mode, tol):
+@pytest.mark.parametrize("rows,dense,rank,down,up,grads", [
+    (2003, 2088, 2056, B128, B128, B128), (4100, 1032, 2184, B256, B128, (128, 128, 3, 2)),
+    (1537, 3080, 1736, M3, B128, B128),
+    (8300, 1976, 2024, B256, B256, (256, 256, 4, 2)),    # the batch in 4
+    (20500, 1512, 1000, B256, B256, (256, 256, 10, 2)),  # ... in 10 (24 tiles)
+    (33000, 984, 1016, B256, B256, (256, 256, 16, 2)),   # ... in 16 (16 tiles, the last split short)
+    (16500, 984, 1016, B256, B256, (128, 128, 6, 2)),
+    (8100, 2024, 504, M3, B256, (128, 128, 6, 2)),       # down: 256 blocks
+    (2500, 1080, 1064, M3, S64, (128, 128, 2, 3)),
+    (1700, 1984, 1048, S64, M3, (128, 128, 1, 3)),        # fused epilogues on 128 x 128, three stages
+    (1301, 1048, 408, S64, S64, (64, 64, 2, 3)),
+    # fewer rows than a load's clamp, over many column tiles
+    (5, 20488, 64, S64, S64, S64), (5, 30984, 64, S64, M2, M3)])
+def test_products(rows, dense, rank, down, up, grads, mode, tol):
+    plans = [gemm_plan(rows, rank, 16 + dense), gemm_plan(rows, 16 + dense, rank, fused_out=True),
+             gemm_plan(16 + dense, rank, rows, weight_grad=True), gemm_plan(rank, 16 + dense, rows, weight_grad=True)]
+    assert [(p.bm, p.bn, p.splits, p.stages) for p in plans] == [down, up, grads, grads]
     need_gpu()
     dev = "cuda"
     d, L = 16 + dense, 2
