@@ -1060,11 +1060,14 @@ hipError_t launch_stream(const GemmArgs& g, hipStream_t s) {
 // 25 us for 512 x 32 x 160; now 7.2 and 6.9 us (a bare launch takes about 2).
 constexpr int FK = 4;  // k steps (of 16) whose loads are in flight together
 
+// (float weights are the caller's and need be aligned to a float only)
+typedef float f32x4_u_t __attribute__((ext_vector_type(4), aligned(4)));
+
 template <bool KS>
 __device__ __forceinline__ f32x4_t frag_f32(const float* __restrict__ x, int64_t ld, int64_t row, int64_t k, int64_t kend) {
     f32x4_t v;
     if (!KS) {  // kend and k are multiples of 4: a piece is inside or past the end
-        v = *(const f32x4_t*)(x + row * ld + (k < kend ? k : 0));
+        v = *(const f32x4_u_t*)(x + row * ld + (k < kend ? k : 0));
         if (k >= kend) v = f32x4_t{0.f, 0.f, 0.f, 0.f};
     } else {
 #pragma unroll

@@ -15,17 +15,11 @@ from paper_2402_06859_amd.synth import Workload, make_inputs
 pytestmark = pytest.mark.gpu
 
 
-# batch (K of the weight gradients): 1, below and above one step of 16 and one pass of the
-# waves, several passes, long enough to be split over workgroups; rank and width: one
-# remainder, one block, 32-blocks and 64-blocks
-@pytest.mark.parametrize("batch,cat,dense,rank,attn", [
-    (1, 2, 4, 4, False), (17, 2, 8, 12, False), (130, 2, 8, 36, True), (515, 3, 20, 32, False), (2051, 4, 64, 64, False),
-    (4099, 2, 32, 20, False), (300, 60, 64, 128, True)])
-def test_products(batch, cat, dense, rank, attn):
-    need_gpu()
-    wl = Workload("f32", 31, batch, cat, 10_000, 100, 16, dense, 2, rank, attn, "f32", "mul", 1.1)
+def run_and_compare(wl, edit=None):
     inp = make_inputs(wl, bias_std=0.1)
     db = DeviceBatch(wl, inp)
+    if edit is not None:
+        edit(db)
     db.gather()
     db.forward()
     db.backward()
@@ -38,5 +32,35 @@ def test_products(batch, cat, dense, rank, attn):
     errs = [relerr(to_np(db.x_out), xL), relerr(to_np(db.grad_x0), gx0)]
     for l in range(wl.num_layers):
         errs += [relerr(to_np(db.g_w_down[l]), gW[l]), relerr(to_np(db.g_u[l]), gU[l]), relerr(to_np(db.g_bias[l]), gb[l])]
-    print(batch, wl.d, rank, "max rel err %.2g" % max(errs), flush=True)
+    print(wl.batch, wl.d, wl.rank, "max rel err %.2g" % max(errs), flush=True)
     assert max(errs) <= 1e-5
+
+
+# batch (K of the weight gradients): 1, below and above one step of 16 and one pass of the
+# waves, several passes, long enough to be split over workgroups; rank and width: one
+# remainder, one block and several
+@pytest.mark.parametrize("batch,cat,dense,rank,attn", [
+    (1, 2, 4, 4, False), (17, 2, 8, 12, False), (130, 2, 8, 36, True), (515, 3, 20, 32, False), (2051, 4, 64, 64, False),
+    (4099, 2, 32, 20, False), (300, 60, 64, 128, True)])
+def test_products(batch, cat, dense, rank, attn):
+    need_gpu()
+    run_and_compare(Workload("f32", 31, batch, cat, 10_000, 100, 16, dense, 2, rank, attn, "f32", "mul", 1.1))
+
+
+def test_weights_aligned_to_a_float():
+    """Float weights one float past a 16-byte boundary: the fragments' loads ask for no more."""
+    need_gpu()
+
+    def shift(ts):
+        out = []
+        for t in ts:
+            v = torch.empty(t.numel() + 1, device="cuda")[1:].view(t.shape)
+            v.copy_(t)
+            assert v.data_ptr() % 16 == 4
+            out.append(v)
+        return out
+
+    def edit(db):
+        db.w_down, db.u = shift(db.w_down), shift(db.u)
+
+    run_and_compare(Workload("f32", 33, 130, 2, 10_000, 100, 16, 8, 2, 36, True, "f32", "mul", 1.1), edit)
