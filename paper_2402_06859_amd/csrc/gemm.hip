@@ -1207,7 +1207,13 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     if (!bf16) {
         // 64 x 64 blocks (two groups of waves along k) once they fill half the chip, else
         // 32 x 32 blocks whose eight waves split k; weight gradients of a long batch over few
-        // tiles split it over workgroups too, at least 1024 rows (128 per wave) each
+        // tiles split it over workgroups too, at least 1024 rows (128 per wave) each. us, 32 x 32 /
+        // 64 x 64, by 64 x 64 tiles: 2048 x 128 x 1024 (64) 13 / 36; 512 x 1024 x 2048 (128) 34 / 39; 1030 x 1000
+        // x 132 (272) 19 / 14; 2048 x 1024 x 128 (512) 37 / 14; 8192 x 4352 x 512 (8704) 511 / 517. (Weight
+        // gradients, both operands strided, would stay ahead on 32 x 32 blocks further: 4352 x 512 x 8192,
+        // 544 tiles, 517 / 720.) Against the vector kernel that these replaced: a training pass of two layers at
+        // batch 2048, width 1024, rank 128 1065 -> 200 us; batch 8192, 2048, 256 10340 -> 1851; scoring one
+        // row at width 1024, rank 64 282 -> 29.
         const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t32 = ((M + 31) / 32) * ((N + 31) / 32);
         p.bm = p.bn = t64 >= 128 ? 64 : 32;
         const int64_t t = t64 >= 128 ? t64 : t32;

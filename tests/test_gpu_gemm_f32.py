@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_helpers import need_gpu, relerr, to_np
+from gpu_helpers import gemm_plan, need_gpu, relerr, to_np
 from paper_2402_06859_amd.step import DeviceBatch
 from paper_2402_06859_amd.synth import Workload, make_inputs
 
@@ -38,13 +38,26 @@ def run_and_compare(wl, edit=None):
 
 # batch (K of the weight gradients): 1, below and above one step of 16 and one pass of the
 # waves, several passes, long enough to be split over workgroups; rank and width: one
-# remainder, one block and several
+# remainder, one block and several, all on 32 x 32 blocks but the last's up and gx
 @pytest.mark.parametrize("batch,cat,dense,rank,attn", [
     (1, 2, 4, 4, False), (17, 2, 8, 12, False), (130, 2, 8, 36, True), (515, 3, 20, 32, False), (2051, 4, 64, 64, False),
-    (4099, 2, 32, 20, False), (300, 60, 64, 128, True)])
+    (4099, 2, 32, 20, False), (300, 60, 64, 128, True), (1030, 31, 492, 132, False)])
 def test_products(batch, cat, dense, rank, attn):
     need_gpu()
     run_and_compare(Workload("f32", 31, batch, cat, 10_000, 100, 16, dense, 2, rank, attn, "f32", "mul", 1.1))
+
+
+# 64 x 64 blocks (four waves side by side, two groups along k): all six products, every
+# combination of contiguous and strided operands, with remainders of rows, columns and k
+# (1030, 988 and 532: none a multiple of 64 or of a pass of 128 k)
+@pytest.mark.parametrize("batch,cat,dense,rank", [(1030, 31, 492, 532), (2053, 31, 492, 532)])
+def test_products_of_64_blocks(batch, cat, dense, rank):
+    need_gpu()
+    d = 16 * cat + dense
+    for M, N, K, grad in ((batch, rank, d, False), (batch, d, rank, False), (d, rank, batch, True), (rank, d, batch, True)):
+        p = gemm_plan(M, N, K, "f32", grad)
+        assert (p.bm, p.bn) == (64, 64)
+    run_and_compare(Workload("f32", 32, batch, cat, 10_000, 100, 16, dense, 1, rank, False, "f32", "mul", 1.1))
 
 
 def test_weights_aligned_to_a_float():
