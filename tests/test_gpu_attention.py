@@ -96,41 +96,48 @@ def test_degenerate_ranges(rank, what):
     compare(Workload("att_deg", 22, 5, 4, 20_000, 150, 16, 64, 1, rank, True, "bf16", "sum", 1.1), edit)
 
 
-# 192 and 256: one wave per sample; 264, 520 and 1024: four; spread: of the logits (16 to 96 panels)
-@pytest.mark.parametrize("rank,spread", [(192, 1.0), (256, 0.3), (256, 3.0), (264, 1.0), (512, 3.0), (520, 1.0),
-                                         (1024, 1.0)])
-def test_panel_sums_precision(rank, spread):
-    """The panel sums' error before [gv|gq|gk] are stored as bf16. Sample b of x0 is the unit
-    vector e_b, so that its v, q, k are column b of W and its gh row b of U, exactly, and
-    column b of W's gradient holds its stored [gv|gq|gk]; skip_beta is 0, so that gv is the
-    softmax's sum alone. How many stored values are not the float64 value's bf16 measures
-    the error: one relative to a value of eps flips a share of about eps / 2^-7.5 (the spacing).
-    Rounding the exponentials to f16 (2^-11) in every sum, as the direct form does, flips
-    3 to 10% (the same sums evaluated in float64 with that one rounding); float sums of hi +
-    lo pairs below 1% on average. Bar: 1%."""
-    need_gpu()
-    dev, B, d = "cuda", 8, 64
+def one_hot_layer(rank, spread, B, seed, edit=None, **cfg):
+    """One layer over B unit vectors: sample b of x0 is e_b, so its v, q, k are column b of W and its gh row
+    b of U, exactly, and column b of W's gradient holds its stored [gv|gq|gk]. Returns the float64
+    [B, 1, r] v and k, [B, r, 1] q and gh, the stored gradient [3 r, B] and the saved buffer."""
+    dev, d = "cuda", 64
     g = torch.Generator(device=dev)
-    g.manual_seed(rank)
+    g.manual_seed(seed)
     rand = lambda *s: torch.randn(*s, device=dev, generator=g)
     W = rand(3 * rank, d)
     W[rank:2 * rank] *= spread
     W, U, b = W.bfloat16(), rand(d, rank).bfloat16(), torch.zeros(d, dtype=torch.bfloat16, device=dev)
+    if edit is not None:
+        edit(W)
     x0 = torch.zeros(B, d, dtype=torch.bfloat16, device=dev)
     x0[range(B), range(B)] = 1
-    lib = Rdcn(make_config(B, 1, 16, d - 16, rank, 1, 40, 40, 1600, attn_alpha=1.0, skip_beta=0.0))
-    saved, scratch = (torch.empty(n, dtype=torch.uint8, device=dev) for n in lib.workspace_bytes(B))
+    lib = Rdcn(make_config(B, 1, 16, d - 16, rank, 1, 40, 40, 1600, attn_alpha=1.0, **cfg))
+    saved, scratch = (torch.zeros(n, dtype=torch.uint8, device=dev) for n in lib.workspace_bytes(B))
     x_out, gx0 = torch.empty_like(x0), torch.empty(B, d, device=dev)
     gW, gU, gb = (torch.empty(t.shape, device=dev) for t in (W, U, b))
     lib.rdcn_forward(B, x0, [W], [U], [b], x_out, saved, scratch)
     lib.rdcn_backward(B, x0, [W], [U], [b], saved, torch.ones_like(x0), gx0, [gW], [gU], [gb], scratch)
     torch.cuda.synchronize()
-    v, q, k = (W[i * rank:(i + 1) * rank, :B].double().t()[:, None, :] for i in range(3))  # [B, 1, r]
-    go, q = U[:B].double()[:, :, None], q.transpose(1, 2)                                  # [B, r, 1]
+    assert lib.check_device_errors() == 0
+    v, q, k = (W[i * rank:(i + 1) * rank, :B].double().t()[:, None, :] for i in range(3))
+    return v, q.transpose(1, 2), k, U[:B].double()[:, :, None], gW[:, :B].double(), saved
+
+
+# 192 and 256: one wave per sample; 264, 520 and 1024: four; spread: of the logits (16 to 96 panels)
+@pytest.mark.parametrize("rank,spread", [(192, 1.0), (256, 0.3), (256, 3.0), (264, 1.0), (512, 3.0), (520, 1.0),
+                                         (1024, 1.0)])
+def test_panel_sums_precision(rank, spread):
+    """The panel sums' error before [gv|gq|gk] are stored as bf16 (exact inputs; skip_beta is 0, so
+    that gv is the softmax's sum alone). How many stored values are not the float64 value's bf16 measures
+    the error: one relative to a value of eps flips a share of about eps / 2^-7.5 (the spacing).
+    Rounding the exponentials to f16 (2^-11) in every sum, as the direct form does, flips
+    3 to 10% (the same sums evaluated in float64 with that one rounding); float sums of hi +
+    lo pairs below 1% on average. Bar: 1%."""
+    need_gpu()
+    v, q, k, go, got, _ = one_hot_layer(rank, spread, 8, rank, skip_beta=0.0)
     A = torch.softmax(q * k, 2)
     D = A * (v - (A * v).sum(2, keepdim=True))
     ref = torch.cat([(A * go).sum(1), (go * D * k).sum(2), (D * go * q).sum(1)], 1).t()    # [3 r, B]
-    got = gW[:, :B].double()
     assert torch.equal(got, got.bfloat16().double())
     shares = []
     for i in range(3):
@@ -139,3 +146,63 @@ def test_panel_sums_precision(rank, spread):
         shares.append(float((y.float().bfloat16().double() != x)[big].double().mean()))
     print(rank, spread, "flipped roundings gv %.4f gq %.4f gk %.4f" % tuple(shares), flush=True)
     assert sum(shares) / 3 <= 0.01
+
+
+# 120: direct sums; 128, 136 and 256: panels of one wave; 264, 520, 1024: of four; spread 60:
+# samples beyond the panels, in the same kernels
+@pytest.mark.parametrize("mode", ["hilo", "f16"])
+@pytest.mark.parametrize("rank,spread", [(120, 1.0), (128, 1.0), (136, 1.0), (256, 1.0), (256, 60.0), (264, 1.0), (520, 1.0),
+                                         (520, 60.0), (1024, 1.0)])
+def test_second_planes_of_h(rank, spread, mode):
+    """h as the forward keeps it: bf16, and a second plane with the bf16 rounding's remainder or the
+    f16 value. The saved buffer of one layer starts with [v|q|k] (float), then the two planes, each
+    256-byte aligned. Bars: what the planes hold (2^-17 of h, or 2^-11 for f16) in the largest element
+    and the sums' 2^-11 (one f16 rounding of the exponentials, direct form) or 2^-15 in norm."""
+    need_gpu()
+    B = 5
+    v, q, k, _, _, saved = one_hot_layer(rank, spread, B, 100 + rank, activation_mode=mode)
+    h = (v + (torch.softmax(q * k, 2) * v).sum(2)[:, None, :])[:, 0]
+    al = lambda n: -(-n // 256) * 256
+    o1 = al(B * 3 * rank * 4)
+    o2 = o1 + al(B * rank * 2)
+    plane = lambda o, dt: saved[o:o + B * rank * 2].view(dt).view(B, rank).double()
+    hi = plane(o1, torch.bfloat16)
+    full = hi + plane(o2, torch.bfloat16) if mode == "hilo" else plane(o2, torch.float16)
+    sums = 2.0 ** -11 if rank < 128 or spread > 1 else 2.0 ** -15
+    held = 2.0 ** -17 if mode == "hilo" else 2.0 ** -11
+    err = float((full - h).norm() / h.norm())
+    print(rank, spread, mode, "rel err %.2g" % err, flush=True)
+    assert err <= sums + held
+    assert float(((hi - full).abs() / full.abs().clamp_min(1e-3)).max()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("rank", [120, 136, 256, 520, 1024])
+@pytest.mark.parametrize("what,part,value", [("query", 1, "nan"), ("query", 1, "inf"), ("key", 2, "nan"), ("key", 2, "inf"),
+                                             ("value", 0, "nan")])
+def test_nonfinite_inputs(rank, what, part, value):
+    """One non-finite coordinate: W has it in sample 1's column, and the products with the other samples' zeros
+    make theirs NaN. h is NaN wherever float64 has NaN; a bad query leaves the other rows within the
+    usual bar (in the direct form all but row 7 + 16, whose exponentials share a matrix operand's
+    column with row 7's: zero times NaN)."""
+    need_gpu()
+    B = 6
+
+    def edit(W):
+        W[part * rank + 7, 1] = float(value)
+
+    # q, k, v as the projection left them, and h (bf16), from the saved buffer
+    saved = one_hot_layer(rank, 1.0, B, 7, edit)[5]
+    n = B * 3 * rank * 4
+    P = saved[:n].view(torch.float32).view(B, 3, rank).double()
+    v, q, k = P[:, 0, None, :], P[:, 1, :, None], P[:, 2, None, :]
+    h = v[:, 0] + (torch.softmax(q * k, 2) * v).sum(2)
+    o1 = -(-n // 256) * 256
+    hd = saved[o1:o1 + B * rank * 2].view(torch.bfloat16).view(B, rank).double()
+    print(rank, what, value, "NaN of %d: %d, device %d" % (h.numel(), h.isnan().sum(), hd.isnan().sum()), flush=True)
+    assert hd[h.isnan()].isnan().all()
+    if what == "query":
+        rest = h.isfinite()
+        assert rest.sum() == B * (rank - 1)
+        if rank < 128:
+            rest[:, 7 + 16] = False
+        assert float((hd - h)[rest].norm() / h[rest].norm()) <= TOL
