@@ -898,7 +898,7 @@ __device__ __forceinline__ void attn_fwd_direct(int r, int rpad, float alpha, fl
         __syncthreads();
         big = uniform_f(sample_max<W>(pw + 2 * 16 * ATT_NT, attn_fwd_wave_floats(), 0));
     }
-    const bool fast = big < ATT_F16_SAFE;  // false for NaN too
+    const bool fast = big < ATT_F16_SAFE;  // (infinities take the FMAs; the maxima pass over NaN, which spreads by itself)
 #pragma unroll
     for (int u = 0; u < RPL; ++u) {
         const int il = 64 * u + lane;
@@ -1315,7 +1315,7 @@ __device__ __forceinline__ void attn_bwd_direct(int r, int rpad, float alpha, fl
         mb = sample_max<W>(slots, attn_bwd_wave_floats(), 2);
         mc = sample_max<W>(slots, attn_bwd_wave_floats(), 3);
     }
-    const bool fast = uniform_f(big) < ATT_F16_SAFE;  // the forward's decision (false for NaN too)
+    const bool fast = uniform_f(big) < ATT_F16_SAFE;  // the forward's decision
     const float as = uniform_f(pow2_ceil(ma)), bs = uniform_f(pow2_ceil(mb)), cs = uniform_f(pow2_ceil(mc));
     const float ias = 1.0f / as, ibs = 1.0f / bs, ics = 1.0f / cs;  // exact: powers of two
 #pragma unroll

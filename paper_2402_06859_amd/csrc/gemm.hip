@@ -13,8 +13,9 @@
 //
 // Tiling: 64 x 64 and 128 x 128 blocks use 256 threads = 4 waves in a 2 x 2 grid,
 // each wave owning a (BM/2) x (BN/2) block of 16 x 16 MFMA tiles
-// (v_mfma_f32_16x16x32_bf16); large products use 256 x 256 or 256 x 128 blocks of
-// 8 waves with 32 x 32 tiles (v_mfma_f32_32x32x16_bf16). Each K step of 64 is one
+// (v_mfma_f32_16x16x32_bf16), or of 32 x 32 tiles (v_mfma_f32_32x32x16_bf16) in the 128 x 128
+// blocks of three stages; large products use 256 x 256 or 256 x 128 blocks of
+// 8 waves with 32 x 32 tiles. Few rows take the streamed blocks further down. Each K step of 64 is one
 // stage of a 2- or 3-stage ring in LDS, filled by direct global-to-LDS loads one or
 // two steps ahead of the multiply (a scalar base advanced along K plus per-lane offsets
 // computed once per block; a tail stage's positions past K are loaded from a block of
@@ -282,8 +283,8 @@ __device__ __forceinline__ int xcd_remap(int id, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// LDS layouts (one stage = one KB-deep slice of A and of B; KB = 64 in every launch,
-// the layouts also hold for KB = 32):
+// LDS layouts (one stage = one KB-deep slice of A and of B; KB = 64, or 32 in the deeper of the
+// streamed blocks):
 //  K-contiguous operand, ROWS x KB bf16: row r holds KB/8 chunks of 16 bytes; the
 //    chunk of logical k-block kc sits in slot kc ^ kc_swz(r) (((r >> 1) & 7) for KB = 64).
 //    Two rows share a 256-byte bank window, so 16 consecutive rows reading the same kc hit 16
@@ -452,37 +453,6 @@ __device__ __forceinline__ bf16x8_t load_frag(const bf16_t* lds, int rt, int ks,
     }
 }
 
-// MFMA fragment (32 rows x 16 k) for v_mfma_f32_32x32x16_bf16: lane l holds row
-// rt + l % 32 and the 8 k values ks + 8 (l / 32) .. + 7. K-strided operands use the
-// same transposing reads as above, each 16-lane group G supplying row chunk
-// rt / 16 + (G & 1) and k rows from ks + 8 (G >> 1).
-template <int ROWS, bool KS, int KB>
-__device__ __forceinline__ bf16x8_t load_frag32(const bf16_t* lds, int rt, int ks, int lane) {
-    if (!KS) {
-        const int r = rt + (lane & 31);
-        const int kc = ks / 8 + (lane >> 5);
-        return __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(lds + r * KB + ((kc ^ kc_swz<KB>(r)) * 8)));
-    } else {
-        const int i = lane & 15, G = lane >> 4;
-        const int c = rt / 16 + (G & 1);
-        const int kb = ks + 8 * (G >> 1);
-        s16x4_t lo, hi;
-        {
-            const int kr = kb + (i >> 2);
-            const int off = kr * ROWS + ((c ^ kstr_swz<ROWS>(kr)) * 16) + (i & 3) * 4;
-            lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4_t*)(lds + off));
-        }
-        {
-            const int kr = kb + 4 + (i >> 2);
-            const int off = kr * ROWS + ((c ^ kstr_swz<ROWS>(kr)) * 16) + (i & 3) * 4;
-            hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4_t*)(lds + off));
-        }
-        typedef short s16x8_t __attribute__((ext_vector_type(8)));
-        const s16x8_t v = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        return __builtin_bit_cast(bf16x8_t, v);
-    }
-}
-
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ void wait_vmcnt(int n) {
@@ -587,9 +557,12 @@ struct Pipe {
         stage_load<BN, BKS, NW, KB>(b, c.g->ldb, c.g->N, c.n0, k0, c.kend, buf + BM * KB, wave, lane);
     }
 
-    // Fragments of 32 x 32 tiles (rows x 16 k) by LDS byte address, layouts as load_frag32:
-    // tile i of a wave and substep s differ from tile 0, substep 0 by an XOR of two address
-    // bits of the swizzled slot and by constants that go into the instruction's offset.
+    // Fragments of 32 x 32 tiles (32 rows x 16 k, v_mfma_f32_32x32x16_bf16) by LDS byte address: lane
+    // l holds row l % 32 of the tile and the 8 k values 8 (l / 32) .. + 7 of the substep. K-strided
+    // operands use the transposing reads of load_frag, each 16-lane group G supplying row chunk
+    // G & 1 and k rows from 8 (G >> 1). Tile i of a wave and substep s differ from tile 0,
+    // substep 0 by an XOR of two address bits of the swizzled slot and by constants that go
+    // into the instruction's offset.
     template <int ROWS, bool KS>
     __device__ __forceinline__ static uint32_t frag_base(const bf16_t* operand, int wrow, int lane) {
         if (!KS) {
@@ -628,7 +601,7 @@ struct Pipe {
     __device__ __forceinline__ static void loop32(const Ctx& c, bf16_t* smem, acc_t (&acc)[TM][TN]) {
         const int lane = c.tid & 63, wave = c.tid >> 6, wm = wave / WN, wn = wave % WN;
         constexpr int NS = KB / 16;  // substeps
-        static_assert(!M32 || NS % 2 == 0, "the fragment buffers alternate");
+        static_assert(M32 && NS % 2 == 0, "the fragment buffers alternate");
         static_assert(ST == 2 || ST == 3, "rings of two or three stages");
         bf16x8_t af[2][TM], bfr[2][TN];
         uint32_t abase_l = frag_base<BM, AKS>(smem, wm * (BM / WM), lane);
@@ -683,7 +656,7 @@ struct Pipe {
         for (int f = 0; f < TM + TN; ++f) frag(f, 0, 0, 0);
         constexpr int MU = TM * TN;  // multiplies per substep
         // fragments read after each of them, so that the last two leave time for the last read
-        constexpr int RPM = M32 ? (TM + TN + MU - 3) / (MU - 2) : 1;
+        constexpr int RPM = (TM + TN + MU - 3) / (MU - 2);
         uint32_t cur = 0;
         auto step = [&](int kt, auto refill_c) __attribute__((always_inline)) {
             constexpr bool REFILL = decltype(refill_c)::value;
@@ -877,7 +850,7 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 2 : 1, WM * WN == 8 ? 2 : 8)))
         // ring of ST stages: step kt multiplies stage kt and fills slot (kt + ST - 1) % ST
         bf16_t* const s0 = smem;
         bf16_t* const s1 = smem + P::STAGE_ELEMS;
-        bf16_t* const s2 = smem + (ST >= 3 ? 2 : 0) * P::STAGE_ELEMS;
+        bf16_t* const s2 = smem + (ST - 1) * P::STAGE_ELEMS;
 #pragma unroll
         for (int u = 0; u < ST - 1; ++u) P::issue(c, u, smem + u * P::STAGE_ELEMS);
         if constexpr (ST == 2) {  // unrolled: fixed buffer pointers in each step
@@ -886,20 +859,14 @@ __attribute__((amdgpu_waves_per_eu(WM * WN == 8 ? 2 : 1, WM * WN == 8 ? 2 : 8)))
                 if (kt + 1 >= c.ntot) break;
                 P::step(c, s1, s0, kt + 1, acc);
             }
-        } else if constexpr (ST == 3) {
+        } else {
+            static_assert(ST == 3, "rings of two or three stages");
             for (int kt = 0; kt < c.ntot; kt += 3) {
                 P::step(c, s0, s2, kt, acc);
                 if (kt + 1 >= c.ntot) break;
                 P::step(c, s1, s0, kt + 1, acc);
                 if (kt + 2 >= c.ntot) break;
                 P::step(c, s2, s1, kt + 2, acc);
-            }
-        } else {
-            int cur = 0;
-            for (int kt = 0; kt < c.ntot; ++kt) {
-                const int nxt = cur == 0 ? ST - 1 : cur - 1;  // (kt + ST - 1) % ST
-                P::step(c, smem + cur * P::STAGE_ELEMS, smem + nxt * P::STAGE_ELEMS, kt, acc);
-                cur = cur + 1 == ST ? 0 : cur + 1;
             }
         }
     }
@@ -1339,7 +1306,9 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStrea
         //   K 10624, N 3072: 16 rows, 192 tiles 13.3 / 48.3; 50 rows, 192 tiles 17.5 / 48.5;
         //                    128 rows, 192 tiles 33.5 / 48.6; 256 rows, 384 tiles 62.9 / 49.2
         //   K 256, N 1856:   128 rows, 232 tiles 4.6 / 5.6; 256 rows, 464 tiles 6.9 / 5.8
-        // (64 x 32 blocks run shorter stages, which pay only on a deep K).
+        // (64 x 32 blocks run shorter stages; at K 256 they and the 64 x 64 ones are level, 6.5 / 6.6 us
+        // for 64 x 8192. Between K 512 and the line at 1536 they would be ahead: 300 x 1024 x 512
+        // 6.5 / 7.5, 128 x 4096 x 1024 8.2 / 9.9.)
         auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
         if (tiles(16, 16) <= 256) return launch_stream<1, 1, 2, 64>(ga, s);
         if (tiles(32, 32) <= 256) return launch_stream<2, 2, 2, 64>(ga, s);
@@ -1357,7 +1326,6 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmPlan& p, bool bf16, hipStrea
         if (p.stages == 2) return launch_tile<128, 128, 2, 2, 2, false, bf16_t>(ga, p.splits, s);
         return launch_tile<128, 128, 3, 2, 2, true, bf16_t>(ga, p.splits, s);
     }
-    if (p.stages == 2) return launch_tile<64, 64, 2, 2, 2, false, bf16_t>(ga, p.splits, s);
     return launch_tile<64, 64, 3, 2, 2, false, bf16_t>(ga, p.splits, s);
 }
 
