@@ -41,17 +41,20 @@ PEAK_HBM_GBS = 8000.0
 EXP_SLOTS = 2.0
 # Exponential rate of the chip: one wave-wide v_exp_f32 issues every 8 clocks per SIMD
 # (measured: 8.1 clk; half the rate of a plain VALU op), so 256 CUs x 4 SIMDs x 8 lanes
-# per clock x 2.4 GHz = 19.66 T exp/s. The attention kernels' roofline is this rate.
+# per clock x 2.4 GHz = 19.66 T exp/s.
 EXP_PEAK_PER_S = 256 * 4 * 8 * 2.4e9
 # Measured rate of independent exp + add pairs over all CUs (an exponential and one
 # more VALU op per pair, as a softmax needs at least): a practical ceiling beside the peak.
 EXP_ADD_MEASURED_PER_S = 14.7e12
-# Measured rates of the attention inner loop's instruction mix run alone (per lane: 16
+# Measured rates of the direct attention sums' inner loop's instruction mix run alone (per lane: 16
 # exponentials, 8 packed conversions to f16, one 32x32x8 and two 16x16x32 f16 MFMAs,
 # 8 waves per SIMD), and of exponentials alone: what the exponent loop can reach
 # without loads, barriers or per-sample set-up.
 EXP_LOOP_MIX_MEASURED_PER_S = 13.5e12
 EXP_ONLY_MEASURED_PER_S = 17.4e12
+# Ranks from which the bf16 attention kernels take panel sums, which evaluate one exponential per (panel,
+# key) instead of one per (query, key) pair; how many panels depends on the scores.
+PANEL_RANK = {"fwd_attention": 128, "bwd_attention": 192}
 
 
 def kernel_work(wl, B: int) -> dict:
@@ -63,9 +66,10 @@ def kernel_work(wl, B: int) -> dict:
     (query, key) pair: the exponent argument (one FMA = 2), the exponential
     (EXP_SLOTS FMA slots = 4) and, for bf16 models whose sums run on the matrix
     cores, half a packed f16 conversion (1); their backward evaluates every pair
-    once (the forward saved each row's normaliser). Float-storage models
-    accumulate on the vector ALU instead (forward + 3 flops per pair; backward
-    evaluates every pair twice, + 11 flops).
+    once (the forward saved each row's normaliser). At the ranks of the panel sums
+    the exponentials depend on the data: alu_ops is 0 there until with_counted_exps
+    fills in a counter's. Float-storage models accumulate on the vector ALU instead
+    (forward + 3 flops per pair; backward evaluates every pair twice, + 11 flops).
     """
     d, r, n = wl.d, wl.rank, wl.n_proj
     nr = n * r
@@ -84,9 +88,11 @@ def kernel_work(wl, B: int) -> dict:
     exp_f = 2.0 * EXP_SLOTS
     pair_fwd = (2.0 + exp_f + 1.0) if wl.dtype == "bf16" else (2.0 + exp_f + 3.0)
     pair_bwd = (2.0 + exp_f + 1.0) if wl.dtype == "bf16" else (2 * (2.0 + exp_f) + 11.0)
-    # saved per row by the matrix-core forward, counted as four floats: (o, Z) and two row sums (the
-    # kernels keep the sums' one combination that the query gradient needs, so three are moved)
-    stats = 4 * r * 4 if wl.dtype == "bf16" else 0
+    if wl.dtype == "bf16":
+        pair_fwd, pair_bwd = (0.0 if r >= PANEL_RANK[k] else p
+                              for k, p in (("fwd_attention", pair_fwd), ("bwd_attention", pair_bwd)))
+    # saved per row by the matrix-core forward: o, Z and the value the query gradient needs
+    stats = 3 * r * 4 if wl.dtype == "bf16" else 0
     # h, and its second plane when the activations are held as f16 or as bf16 hi + lo
     h_out = r * eb * (2 if wl.act_mode in ("f16", "hilo") else 1)
     w["fwd_attention"] = (0.0, B * (3 * r * 4 + h_out + stats), pair_fwd * B * r * r)
@@ -163,10 +169,11 @@ def _radix_passes(maxkey: int) -> int:
 def roofline_for(name: str, work: tuple, avg_s: float, bf16: bool) -> dict:
     flops, nbytes, alu = work
     if bf16 and name in ("fwd_attention", "bwd_attention"):
-        # exponential-bound: one exp per (query, key) pair; alu holds 7 FMA-equivalent flops per pair
+        # the larger of its bytes and its exponentials; alu holds 7 FMA-equivalent flops per exponential
         exps = alu / 7.0
-        return {"bound": "exp", "achieved": exps / avg_s / 1e12, "peak": EXP_PEAK_PER_S / 1e12, "unit": "Texp/s"}
-    if alu > 0:
+        if exps / EXP_PEAK_PER_S >= nbytes / (PEAK_HBM_GBS * 1e9):
+            return {"bound": "exp", "achieved": exps / avg_s / 1e12, "peak": EXP_PEAK_PER_S / 1e12, "unit": "Texp/s"}
+    elif alu > 0:
         return {"bound": "alu", "achieved": alu / avg_s / 1e12, "peak": PEAK_F32_UNPACKED_TFLOPS, "unit": "TFLOP/s"}
     peak_f = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_TFLOPS
     t_f = flops / (peak_f * 1e12)
@@ -248,6 +255,17 @@ def counter_record(prefix: str, kernel: str, workload: str):
     return None
 
 
+def with_counted_exps(work: dict, tag: str) -> dict:
+    """kernel_work with the exponentials of the attention kernels' panel sums taken from the counter
+    records under profiles/ (while the kernels' sources are unchanged)."""
+    out = dict(work)
+    for k in PANEL_RANK:
+        rec = counter_record("trans", k, tag)
+        if k in out and out[k][2] == 0.0 and rec is not None:
+            out[k] = (out[k][0], out[k][1], 7.0 * rec["exps_per_launch"])
+    return out
+
+
 def phase_rooflines(work: dict, prof: dict, bf16: bool) -> dict:
     """Every timed kernel against its own bound: {kernel: {bound, achieved, unit, frac}}."""
     out = {}
@@ -293,26 +311,24 @@ def mfma_counter_rates(wl, tag: str, prof: dict) -> dict:
     return out
 
 
-def attention_exp_rate(wl, tag: str, B: int, prof: dict):
-    """(query, key) pairs per second of the attention kernels as exponentials per second (one
-    per pair in the forward and one in the backward; the panel sums evaluate far fewer, so the
-    rate can pass the chip's) against the chip's exponential rate and against the
-    measured exp + add rate."""
+def attention_rates(wl, tag: str, B: int, prof: dict):
+    """(query, key) pairs per second of the attention kernels, and with a counter record of the
+    same kernel and workload (SQ_INSTS_VALU_TRANS_F32 x 64) the exponentials they evaluate:
+    per launch, over the pairs, and per second against the chip's exponential rate."""
     if not wl.attention:
         return None
     out = {}
     for k in ("fwd_attention", "bwd_attention"):
         ms, n = prof.get(k, (0.0, 0))
         if n:
-            rate = B * wl.rank * wl.rank / (ms / n / 1e3)
-            out[k] = {"exp_per_s": rate, "frac_of_peak": rate / EXP_PEAK_PER_S,
-                      "frac_of_measured_exp_add_rate": rate / EXP_ADD_MEASURED_PER_S,
-                      "frac_of_measured_loop_mix_rate": rate / EXP_LOOP_MIX_MEASURED_PER_S}
+            pairs, sec = B * wl.rank * wl.rank, ms / n / 1e3
+            out[k] = {"pairs_per_s": pairs / sec}
             rec = counter_record("trans", k, tag)
-            if rec is not None:  # SQ_INSTS_VALU_TRANS_F32 x 64 of the same kernel and workload
-                out[k]["counter_exps_per_launch"] = rec["exps_per_launch"]
-                out[k]["counter_exps_over_pairs"] = rec["exps_per_launch"] / (B * wl.rank * wl.rank)
-                out[k]["valu_instr_per_exp_lane"] = rec["valu_instr_per_launch"] * 64 / rec["exps_per_launch"]
+            if rec is not None:
+                exps = rec["exps_per_launch"]
+                out[k].update(counter_exps_per_launch=exps, counter_exps_over_pairs=exps / pairs,
+                              counter_exp_per_s=exps / sec, counter_exp_frac_of_peak=exps / sec / EXP_PEAK_PER_S,
+                              valu_instr_per_exp_lane=rec["valu_instr_per_launch"] * 64 / exps)
     return out
 
 
@@ -619,7 +635,7 @@ def main():
     db.lib.profile_start(4096)
     step()
     prof = db.lib.profile_stop()
-    work = kernel_work(wl, B)
+    work = with_counted_exps(kernel_work(wl, B), profile_tag(wl, head))
     if head is not None:
         work.update(head_work(wl, head, B))
     dominant = max((k for k in prof if k in work), key=lambda k: prof[k][0])
@@ -681,7 +697,7 @@ def main():
         "gather_counter_gbps": counter_gbps,
         "gather_model_gbps": (work["gather"][1] / gather_s / 1e9) if gather_s > 0 else None,
         "gather_model_frac": (work["gather"][1] / gather_s / 1e9 / PEAK_HBM_GBS) if gather_s > 0 else None,
-        "attention_exp_per_s": attention_exp_rate(wl, profile_tag(wl, head), B, prof),
+        "attention": attention_rates(wl, profile_tag(wl, head), B, prof),
         "phases": phase_rooflines(work, prof, wl.dtype == "bf16"),
         "kernels": kernels,
     }

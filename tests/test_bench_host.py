@@ -3,6 +3,7 @@ the roofline bound selection, and the lookup of counter records by workload tag 
 source hash."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -41,30 +42,43 @@ def test_work_model_large_products():
     w = bench.kernel_work(wl, wl.batch)
     assert w["fwd_down_gemm"][0] == pytest.approx(2.139e12, rel=1e-3)   # 2 * 32768 * 3072 * 10624
     assert w["fwd_up_gemm"][0] == pytest.approx(7.13e11, rel=1e-3)
-    # one exponential per (query, key) pair, carried as 7 FMA-equivalent flops per pair
-    assert w["fwd_attention"][2] / 7.0 == pytest.approx(wl.batch * wl.rank * wl.rank)
+    # rank 1024: panel sums, whose exponentials are counted and not modelled
+    assert w["fwd_attention"][2] == w["bwd_attention"][2] == 0.0
+    # below their ranks one exponential per (query, key) pair, carried as 7 FMA-equivalent flops
+    for rank, fwd, bwd in ((120, 1, 1), (128, 0, 1), (184, 0, 1), (192, 0, 0)):
+        w = bench.kernel_work(wl.with_(rank=rank), wl.batch)
+        assert w["fwd_attention"][2] / 7.0 == pytest.approx(fwd * wl.batch * rank * rank)
+        assert w["bwd_attention"][2] / 7.0 == pytest.approx(bwd * wl.batch * rank * rank)
+
+
+def test_panel_ranks_are_the_kernels():
+    src = open(os.path.join(bench.ROOT, "paper_2402_06859_amd", "csrc", "attention.hip")).read()
+    m = re.search(r"AP_MIN_RANK_FWD = (\d+), AP_MIN_RANK_BWD = (\d+);", src)
+    assert (int(m[1]), int(m[2])) == (bench.PANEL_RANK["fwd_attention"], bench.PANEL_RANK["bwd_attention"])
 
 
 def test_work_model_attention_bytes():
     """Bytes of the attention kernels written out from what they move per sample: the
     forward reads [v|q|k] (float) and writes h (bf16, plus its f16 copy when the
-    activations are held in f16) and four float statistics per row (o, Z, W1, W2); the
+    activations are held in f16) and three float statistics per row (o, Z, D); the
     backward reads [v|q|k], the float gh and the statistics and writes [gv|gq|gk]."""
     wl = WORKLOADS["large"]  # f16 activations
     B, r = wl.batch, wl.rank
     w = bench.kernel_work(wl, B)
-    assert w["fwd_attention"][1] == B * (3 * r * 4 + 2 * r * 2 + 4 * r * 4)
-    assert w["bwd_attention"][1] == B * (3 * r * 4 + r * 4 + 4 * r * 4 + 3 * r * 2)
+    assert w["fwd_attention"][1] == B * (3 * r * 4 + 2 * r * 2 + 3 * r * 4)
+    assert w["bwd_attention"][1] == B * (3 * r * 4 + r * 4 + 3 * r * 4 + 3 * r * 2)
     # up: h, U, bias, x0, x_l in; t, x_{l+1} (f16) and its bf16 copy out
     d = wl.d
     assert w["fwd_up_gemm"][1] == B * r * 2 + d * r * 2 + d * 2 + B * d * 2 * 5
     small = WORKLOADS["small"]  # bf16 activations: one h plane
     ws = bench.kernel_work(small, small.batch)
-    assert ws["fwd_attention"][1] == small.batch * (3 * small.rank * 4 + small.rank * 2 + 4 * small.rank * 4)
+    assert ws["fwd_attention"][1] == small.batch * (3 * small.rank * 4 + small.rank * 2 + 3 * small.rank * 4)
 
 
 def test_roofline_bound_selection():
-    # attention of a bf16 model: exponential-bound, reported in exponentials per second
+    # attention of a bf16 model: the larger of its exponentials and its bytes
+    r = bench.roofline_for("bwd_attention", (0.0, 1e9, 0.0), 1e-3, True)
+    assert r["bound"] == "hbm" and r["achieved"] == pytest.approx(1000.0)
     r = bench.roofline_for("fwd_attention", (0.0, 1e9, 7.0e12), 1e-3, True)
     assert r["bound"] == "exp" and r["unit"] == "Texp/s"
     assert r["achieved"] == pytest.approx(1e12 / 1e-3 / 1e12)
@@ -99,3 +113,13 @@ def test_counter_records_follow_the_sources(tmp_path, monkeypatch):
     assert bench.measured_traffic("gather", "feed") is None
     assert bench.measured_traffic("fwd_attention", "small") is None
     assert bench.counter_record("traffic", "gather", "small")["bytes_per_launch"] == 1234
+    rec = {"kernel": "fwd_attention", "workload": "small", "sha256": sha, "exps_per_launch": 1e9, "valu_instr_per_launch": 5e7}
+    (prof / "y_counters.md").write_text("trans: %s\n" % json.dumps(rec))
+    work = {"fwd_attention": (0.0, 1e6, 0.0), "bwd_attention": (0.0, 1e6, 7e9)}
+    counted = bench.with_counted_exps(work, "small")
+    assert counted == {"fwd_attention": (0.0, 1e6, 7e9), "bwd_attention": (0.0, 1e6, 7e9)}
+    assert bench.with_counted_exps(work, "feed") == work
+    wl = WORKLOADS["small"]
+    rates = bench.attention_rates(wl, "small", wl.batch, {"fwd_attention": (2.0, 1), "bwd_attention": (2.0, 1)})
+    assert rates["fwd_attention"]["counter_exp_per_s"] == pytest.approx(1e9 / 2e-3)
+    assert set(rates["bwd_attention"]) == {"pairs_per_s"}
