@@ -500,22 +500,23 @@ __device__ __forceinline__ f16x8_t frag32(const _Float16* sx, int ld, int lane, 
 // 30 or so) and 128 (96 in the backward) when they reach 130, against r = 256 .. 1024
 // exponentials per row for the direct sums; those stay for samples whose scores need more than
 // 3 r / 8 (r / 4) panels or exceed the f16 range, and for small ranks.
-// The exponentials too are f16 hi + lo pairs. The direct sums round them once, but Z, o and the
-// backward's sums of a row share the rounded values, so that most of the error leaves with the
-// division by Z; panels of rows and panels of keys round different exponentials, and with one f16
-// each the backward's sums were 1.5 to 4 times further from float64 than the direct ones (rank 512,
-// spread 9: gk 5.0e-4 against 2.8e-4, gv 6.8e-4 against 9.7e-5). With pairs in both directions they
-// are within 2e-5 at ranks 136 to 1024, spreads 0.3 to 9 (pairs in the backward alone leave the
-// error of Z and o in gk: 6.4e-4 against 3.8e-4 at rank 1024, spread 9).
+// The backward's exponentials too are f16 hi + lo pairs. The direct sums round them once, but there
+// a row's Z, o and column-sum terms share the rounded values, so that part of the error leaves with
+// the division by Z. Panels of rows and panels of keys round different exponentials: with one f16
+// each, o and D are as close to float64 as the direct ones (0.98 to 1.03 of their error), but the
+// backward's sums 1.2 to 5 times further off (24 draws, rank 512, spread 9: gk 4.7e-4 against 1.9e-4, gv
+// 4.8e-4 against 7.9e-5; rank 1024, spread 1: 5.8e-4 / 3.0e-4, 5.0e-4 / 2.5e-4). With pairs there what is
+// left comes from the forward's Z and o, and is the direct form's error or less (1.3e-4, 4.6e-5; 9.2e-5,
+// 3.4e-5). Pairs in the forward as well would leave 1e-5 (and cost it 9%).
 // Measured (direct -> panel sums, us per launch alone, |logits| up to 30): batch 8192, rank
-// 1024: forward 723 -> 102, backward 742 -> 147; batch 4096, rank 512: 106 -> 32, 109 -> 48;
-// batch 4096, rank 256: 32 -> 17, 32 -> 20; with ten times the logits, rank 1024: 723 -> 491,
-// 743 -> 571. (One f16 per exponential: 94, 139; 29, 46; 16, 19; 399, 510.) What remains is bound by
+// 1024: forward 729 -> 91, backward 749 -> 147; batch 4096, rank 512: 107 -> 28, 109 -> 48;
+// batch 4096, rank 256: 33 -> 15, 32 -> 20; with ten times the logits, rank 1024: 728 -> 383,
+// 750 -> 574. (The backward with one f16 per exponential: 139, 46, 19, 513.) What remains is bound by
 // the vector work around the exponentials (the tiles' powers, the polynomials) and the traffic of
 // [v|q|k], h and the statistics. Where a line between the two forms lies: a panel costs what 2
 // (forward) or 3.2 (backward) of a row's r direct exponentials cost (rank 256, batch 4096: 0.25 and
 // 0.4 us against 0.126), on top of the set-up, and below ranks 128 and 192 the direct sums
-// take no longer than the panels' set-up (rank 128, batch 8192: forward 23 -> 16.5; rank 64, panels
+// take no longer than the panels' set-up (rank 128, batch 8192: forward 23 -> 15; rank 64, panels
 // forced: 12.5 -> 13.7, 13 -> 21). A sample beyond the line pays for the choice and for the
 // panel kernels' registers and LDS: against kernels of the direct sums alone, |logits| of 500 and more,
 // rank 1024 726 -> 759 and 748 -> 780, rank 512 113 -> 115 and 110 -> 126, rank 256 32.3 -> 35.7 and
@@ -725,7 +726,6 @@ __device__ __forceinline__ void attn_fwd_panels(const ScoreRange& R, int r, floa
     const float vs = pow2_ceil(vmax), ivs = 1.0f / vs;  // exact scaling: a power of two
     const float cq = LOG2E * inv_tau * R.Hk;
     const int ng = R.p.n / 16, col = lane & 15;
-    const float m1 = minus_one();
     float2 ov[TPW], zv[TPW], dv[TPW];
 #pragma unroll
     for (int i = 0; i < TPW; ++i) ov[i] = zv[i] = dv[i] = make_float2(0.f, 0.f);
@@ -763,12 +763,9 @@ __device__ __forceinline__ void attn_fwd_panels(const ScoreRange& R, int r, floa
                             float e[8];
 #pragma unroll
                             for (int u = 0; u < 8; ++u) e[u] = __builtin_amdgcn_exp2f(fmaf(yp[g], s8[u], -fabsf(yp[g])));
-                            const u32x4_t ep = as_stored(pack_e(e));
-                            const f16x8_t ef = __builtin_bit_cast(f16x8_t, ep),
-                                          el = __builtin_bit_cast(f16x8_t, pack_e_lo(e, ep, m1));
+                            const f16x8_t ef = __builtin_bit_cast(f16x8_t, pack_e(e));
                             acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, ef, acc[g], 0, 0, 0);
                             acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, ef, acc[g], 0, 0, 0);
-                            acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, el, acc[g], 0, 0, 0);
                         }
                 }
             }
