@@ -1204,7 +1204,8 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     };
     int64_t sp = split(t128);
     // weight gradients of a short batch: 64 x 64 tiles where 128 x 128 ones leave half the
-    // chip idle (1064 x 400 x 1501: 72 blocks 12.9 us, 238 blocks 9.7)
+    // chip idle (1064 x 400 x 1501: 72 blocks 12.9 us, 238 blocks 9.7; batches of 200 to 1500 over
+    // 512 x 512 to 4352 x 384: 0.67 to 0.97 of the time, 512 x 512 over 3000: level)
     if (allow_split && p.bm == 128 && t128 * sp < 128) p.bm = p.bn = 64;
     if (p.bm == 64) sp = split(((M + 63) / 64) * ((N + 63) / 64));
     p.splits = (int)sp;
@@ -1237,8 +1238,8 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool allow_split,
     // Large products (bound by the MFMA rate rather than by L2 -> LDS loads): eight
     // waves on 256-row blocks with 32 x 32 x 16 MFMAs, which halve the bytes loaded
     // per flop; 256 x 256 blocks when they still cover the chip, else 256 x 128 if those
-    // cover more than half of it (8192 x 512 x 4352: 128 blocks of 256 x 128 70 us, 256 of
-    // 128 x 128 53).
+    // cover more than half of it (8192 x 512 x 4352: 128 blocks of 256 x 128 60 us, 256 of
+    // 128 x 128 48; 4096 x 1024 x 2048 34.5 / 28.8, x 4096 54 / 44).
     if ((double)M * (double)N * (double)K >= 8.0e9 && offsets32) {
         // Per 64-deep K step a block needs max(MFMA time, load time): MFMA at ~3600
         // flop/clk per CU, loads at the ~24 B/clk per CU that L2 -> LDS sustains here.
