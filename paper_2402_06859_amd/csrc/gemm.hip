@@ -339,10 +339,12 @@ __device__ __align__(16) const uint32_t kZero16[4] = {0u, 0u, 0u, 0u};
 // Rows past `rows` re-read the last row (their results are discarded); K positions at
 // or past kend read zeros. K-contiguous operands need kend - k0 to be a multiple of 8
 // (a 16-byte piece never straddles kend: K is a multiple of 8 for bf16 models).
-// ROLLED keeps its addresses out of the registers, for the 32 x 32 loop, whose accumulators and
-// fragments need them and which loads one remainder per block with it. The other loops load
-// their partial last stage, its re-reads and, without 32-bit offsets (under 8 rows), every
-// stage with it: unrolled, the address arithmetic of its loads overlaps (the Feed head's training
+// ROLLED keeps its addresses out of the registers and out of the prologue: for the 32 x 32 loop, whose
+// accumulators and fragments need the registers and which loads one remainder per block with it, and for
+// the streamed blocks, where one wave loads one partial stage with it and the hoisted addresses cost each
+// launch (a request of 50 rows, unrolled -> rolled: 69.5 -> 68.1 us; with K remainders 69.9 -> 70.8). The
+// other loops load their partial last stage, its re-reads and, without 32-bit offsets (under 8 rows),
+// every stage with it: unrolled, the address arithmetic of its loads overlaps (the Feed head's training
 // pass at batches 200 to 600, rolled -> unrolled: 420 -> 408 to 674 -> 661 us; requests of 1 to 7 rows
 // at width 13824 or 10624: 74 -> 67 to 72 -> 70).
 template <int ROWS, bool KS, int NW, int KB, bool ROLLED = false>
@@ -930,8 +932,8 @@ __global__ __launch_bounds__(64 * ST_KW) void k_gemm_stream(GemmArgs g) {
 #pragma unroll
             for (int u = 0; u < NIB; ++u) dma16_s(boff[u], sb, lb + 1024u * u);
         } else {
-            stage_load<BM, false, 1, KB>(a, g.lda, g.M, m0, k0, g.K, buf, 0, lane);
-            stage_load<BN, false, 1, KB>(b, g.ldb, g.N, n0, k0, g.K, buf + BM * KB, 0, lane);
+            stage_load<BM, false, 1, KB, true>(a, g.lda, g.M, m0, k0, g.K, buf, 0, lane);
+            stage_load<BN, false, 1, KB, true>(b, g.ldb, g.N, n0, k0, g.K, buf + BM * KB, 0, lane);
         }
     };
 #pragma unroll
