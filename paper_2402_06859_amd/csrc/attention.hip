@@ -509,18 +509,18 @@ __device__ __forceinline__ f16x8_t frag32(const _Float16* sx, int ld, int lane, 
 // left comes from the forward's Z and o, and is the direct form's error or less (1.3e-4, 4.6e-5; 9.2e-5,
 // 3.4e-5). Pairs in the forward as well would leave 1e-5 (and cost it 9%).
 // Measured (direct -> panel sums, us per launch alone, |logits| up to 30): batch 8192, rank
-// 1024: forward 729 -> 91, backward 749 -> 147; batch 4096, rank 512: 107 -> 28, 109 -> 48;
-// batch 4096, rank 256: 33 -> 15, 32 -> 20; with ten times the logits, rank 1024: 728 -> 383,
-// 750 -> 574. (The backward with one f16 per exponential: 139, 46, 19, 513.) What remains is bound by
+// 1024: forward 727 -> 88, backward 747 -> 119; batch 4096, rank 512: 106 -> 28, 108 -> 40;
+// batch 4096, rank 256: 32 -> 15, 32 -> 19; with ten times the logits, rank 1024: 728 -> 381,
+// 746 -> 496. (The backward's pairs cost 2 to 12% of that.) What remains is bound by
 // the vector work around the exponentials (the tiles' powers, the polynomials) and the traffic of
 // [v|q|k], h and the statistics. Where a line between the two forms lies: a panel costs what 2
-// (forward) or 3.2 (backward) of a row's r direct exponentials cost (rank 256, batch 4096: 0.25 and
-// 0.4 us against 0.126), on top of the set-up, and below ranks 128 and 192 the direct sums
+// (forward) or 2.3 (backward) of a row's r direct exponentials cost (rank 256, batch 4096: 0.25 and
+// 0.29 us against 0.126), on top of the set-up, and below ranks 128 and 192 the direct sums
 // take no longer than the panels' set-up (rank 128, batch 8192: forward 23 -> 15; rank 64, panels
 // forced: 12.5 -> 13.7, 13 -> 21). A sample beyond the line pays for the choice and for the
-// panel kernels' registers and LDS: against kernels of the direct sums alone, |logits| of 500 and more,
-// rank 1024 726 -> 759 and 748 -> 780, rank 512 113 -> 115 and 110 -> 126, rank 256 32.3 -> 35.7 and
-// 32.1 -> 35.1 us.
+// panel kernels' registers: against kernels of the direct sums alone, |logits| of 500 and more,
+// rank 1024 726 -> 756 and 746 -> 747, rank 512 112 -> 115 and 109 -> 114, rank 256 32.2 -> 35.5 and
+// 32.4 -> 34 us.
 //
 // Data are handled in tiles of 128 entries, two consecutive entries per lane. A tile's
 // operand matrix is kept in LDS as chunks of 8 entries x 16 rows (16 bytes per row and
@@ -1034,9 +1034,13 @@ __global__ __launch_bounds__(64 * att_block_waves(W)) __attribute__((amdgpu_wave
 }
 
 // LDS of the backward's panel sums, in floats: per wave three tile matrices (a z^t and
-// a o z^t: hi, lo; go/Z z^t: hi in rows 0-7, lo in rows 8-15) and the tile's y values, reused
-// for the wave's moments and the panels' polynomials (pitch 28) as in the forward.
-constexpr int AP_BWD_WAVE = 3 * AP_MAT / 2 + 128;
+// a o z^t: hi, lo; go/Z z^t: hi in rows 0-7, lo in rows 8-15), reused for the wave's moments and the
+// panels' polynomials (pitch 28) as in the forward. The tile's y values lie in the chunks' padding
+// (entries 0-3 of a chunk behind its hi rows, 4-7 behind its lo rows): four waves then take 52 KB and
+// three workgroups share a CU, the three waves per SIMD that the registers allow; with 512 bytes per
+// wave of their own it was two (batch 8192, rank 1024: 147 -> 119 us, rank 512, batch 4096: 48 -> 40;
+// samples left to the direct sums 780 -> 747 and 126 -> 114).
+constexpr int AP_BWD_WAVE = 3 * AP_MAT / 2;
 constexpr int AP_BWD_PITCH = 28;
 static_assert(16 * ap_groups_bwd(1) * AP_BWD_PITCH <= AP_BWD_WAVE, "the polynomials fit the tile");
 static_assert(512 * ap_groups_bwd(4) + 16 * AP_BWD_PITCH * ((ap_groups_bwd(4) + 3) / 4) <= AP_BWD_WAVE,
@@ -1088,7 +1092,7 @@ __device__ __forceinline__ void attn_bwd_panels(const ScoreRange& R, int r, floa
     _Float16* const xh = (_Float16*)region;
     _Float16* const xl = xh + AP_MAT;
     _Float16* const xg = xl + AP_MAT;
-    float* const ty = region + 3 * AP_MAT / 2;
+    const int yw = (lane >> 2) * AP_PITCH + 128 + ((2 * lane) & 2) * 2;  // where the lane's two y go (f16 units)
     constexpr int AP_G = ap_groups_bwd(W);
     auto coef = [&](int p) {  // polynomials of panel p of the sweep
         return W == 1 ? region + p * AP_BWD_PITCH
@@ -1122,15 +1126,15 @@ __device__ __forceinline__ void attn_bwd_panels(const ScoreRange& R, int r, floa
                 put_powers(xh, xl, 0, lane, make_float2(wa.x * ias, wa.y * ias), z);
                 put_powers(xh, xl, 8, lane, make_float2(wo.x * ibs, wo.y * ibs), z);
                 put_powers(xg, xg + 64, 0, lane, make_float2(wg.x * ics, wg.y * ics), z);
-                *(float2*)(ty + 2 * lane) = yy;
+                *(float2*)(((lane & 2) ? xl : xh) + yw) = yy;
                 wave_sync();
                 const int nks = r - j0 < 128 ? (r - j0 + 31) / 32 : 4;
 #pragma unroll 1
                 for (int ks = 0; ks < nks; ++ks) {
                     const f16x8_t ah = panel_frag(xh, ks, lane), al = panel_frag(xl, ks, lane), ag = panel_frag(xg, ks, lane);
                     float y8[8];
-                    *(f32x4_t*)y8 = *(const f32x4_t*)(ty + 32 * ks + 8 * (lane >> 4));
-                    *(f32x4_t*)(y8 + 4) = *(const f32x4_t*)(ty + 32 * ks + 8 * (lane >> 4) + 4);
+                    *(f32x4_t*)y8 = *(const f32x4_t*)(xh + (4 * ks + (lane >> 4)) * AP_PITCH + 128);
+                    *(f32x4_t*)(y8 + 4) = *(const f32x4_t*)(xl + (4 * ks + (lane >> 4)) * AP_PITCH + 128);
 #pragma unroll
                     for (int g = 0; g < AP_G; ++g)
                         if (g < gc) {
